@@ -94,12 +94,12 @@ struct Plan {
   int n_units = 0;
   int n_dunits = 0;                 // degridding units: items of one tile, <= DUNIT_VIS visibilities
   std::vector<int> bunit_off_host;  // d + 1
-  std::vector<int64_t> order_host;  // plan position -> user index
+  std::vector<int> order_host;      // plan position -> user index
   std::vector<int64_t> block_off_host;
 
   // device
   uint2* coord = nullptr;     // M packed (x, y) coordinates, plan order
-  int64_t* order = nullptr;   // M, plan position -> user index
+  int* order = nullptr;       // M, plan position -> user index
   Item* items = nullptr;      // n_items, block order (y = own index)
   Item* titems = nullptr;     // n_items grouped by tile (all blocks), y = index in block order
   // n_items footprint boxes: the smallest and largest row and column of the item's first
@@ -217,7 +217,7 @@ int grid_all(const Plan& p, const float2* v, float2* grid, hipStream_t s);
 int plan_sort(const float* uv, int64_t M, const int64_t* off, int d, int K, int T, int tpa, uint2** packed,
               std::vector<uint64_t>& keys_sorted, std::vector<int>& idx_sorted, hipStream_t s);
 // coord[k] = packed[order[k]] (device arrays of M).
-int plan_gather_coord(const uint2* packed, const int64_t* order, int64_t M, uint2* coord, hipStream_t s);
+int plan_gather_coord(const uint2* packed, const int* order, int64_t M, uint2* coord, hipStream_t s);
 
 // ---- DDE-aware G (dde.hip); used by the functions above when p.dde.on() ----
 int dde_degrid(const Plan& p, const int4* units, int nunits, const Item* items, const uint8_t* mask,
@@ -233,6 +233,8 @@ void dde_destroy(Dde& dd);
 
 // ---- reductions (reduce.hip) ----
 int zero_f32(float* p, size_t n, hipStream_t s);
+// dst = src, n floats (device memory, not overlapping).
+int copy_f32(float* dst, const float* src, size_t n, hipStream_t s);
 int zero_c64(float2* p, size_t n, hipStream_t s);
 // out[0] = sum x^2 (FP64); out holds SUMSQ_SCRATCH doubles.
 constexpr int SUMSQ_SCRATCH = 1025;

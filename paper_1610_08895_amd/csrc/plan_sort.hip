@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void k_plan_keys(const float* __restrict__ uv,
 }
 
 __global__ __launch_bounds__(256) void k_gather_coord(const uint2* __restrict__ packed,
-                                                      const int64_t* __restrict__ order, int64_t M,
+                                                      const int* __restrict__ order, int64_t M,
                                                       uint2* __restrict__ coord) {
   for (int64_t k = int64_t(blockIdx.x) * 256 + threadIdx.x; k < M; k += int64_t(gridDim.x) * 256)
     coord[k] = packed[order[k]];
@@ -112,7 +112,7 @@ int plan_sort(const float* uv, int64_t M, const int64_t* off, int d, int K, int 
   return rc;
 }
 
-int plan_gather_coord(const uint2* packed, const int64_t* order, int64_t M, uint2* coord, hipStream_t s) {
+int plan_gather_coord(const uint2* packed, const int* order, int64_t M, uint2* coord, hipStream_t s) {
   hipLaunchKernelGGL(k_gather_coord, dim3(grid_of(M)), dim3(256), 0, s, packed, order, M, coord);
   RI_LAUNCH_CHECK();
   return RI_OK;

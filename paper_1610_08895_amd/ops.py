@@ -88,8 +88,9 @@ class Plan:
 
     def phi(self, x, y=None, mask=None):
         xp = _dev(x, torch.float32, (self.n, self.n), "x")
-        if y is None:
-            y = torch.zeros(self.M, dtype=torch.complex64, device=x.device)
+        if y is None:  # without a mask every row is written
+            new = torch.empty if mask is None else torch.zeros
+            y = new(self.M, dtype=torch.complex64, device=x.device)
         L.check(L.load().ri_phi(self._h, xp, _dev(y, torch.complex64, (self.M,), "y"), _mask(mask, self.d),
                                 _stream()))
         return y
