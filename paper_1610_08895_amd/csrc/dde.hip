@@ -323,6 +323,48 @@ __global__ __launch_bounds__(DT) void k_dde_merge(float2* __restrict__ grid, con
   }
 }
 
+// The sum of the DDE tiles' patches covering each cell of a gridding tile (neighbours in a fixed
+// order) into that tile's own cells of the patch array (=, or += with ADD); without ADD the
+// rest of its slot, where the plain kernel stores its reach, becomes zero.  One workgroup per
+// gridding tile.
+template <int T, int H, bool ADD>
+__global__ __launch_bounds__(DT) void k_dde_merge_win(float2* __restrict__ sum, const float2* __restrict__ patch,
+                                                  const uint8_t* __restrict__ tile_has, int K, int tpa, int gta) {
+  using G = DdeGeom<T, H>;
+  constexpr int TW = G::TW, R0 = G::R0;
+  static_assert(TW - R0 <= 2 * T && R0 <= T, "a region reaches into the neighbouring tiles only");
+  const int gty = blockIdx.x / gta, gtx = blockIdx.x - (blockIdx.x / gta) * gta;
+  float2* out = sum + size_t(blockIdx.x) * PATCH_CELLS;
+  for (int k = threadIdx.x; k < PATCH_CELLS; k += DT) {
+    const int R = k / PATCH_W, C = k - (k / PATCH_W) * PATCH_W;
+    if (R >= GSIDE || C >= GSIDE) {
+      if (!ADD) out[k] = make_float2(0.f, 0.f);
+      continue;
+    }
+    const int gy = (gty * GSIDE - (KB_J / 2 - 1) + R) & (K - 1), gx = (gtx * GSIDE - (KB_J / 2 - 1) + C) & (K - 1);
+    const int ty = gy / T, iy = gy % T, tx = gx / T, ix = gx % T;
+    float2 acc = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int dy = -1; dy <= 1; ++dy)
+#pragma unroll
+      for (int dx = -1; dx <= 1; ++dx) {
+        const int ly = iy - dy * T + R0, lx = ix - dx * T + R0;
+        if (ly < 0 || ly >= TW || lx < 0 || lx >= TW) continue;
+        const int nt = ((ty + dy + tpa) & (tpa - 1)) * tpa + ((tx + dx + tpa) & (tpa - 1));
+        if (!tile_has[nt]) continue;
+        const float2 h = patch[size_t(nt) * TW * TW + ly * TW + lx];
+        acc.x += h.x;
+        acc.y += h.y;
+      }
+    if (!ADD) {
+      out[k] = acc;
+    } else if (acc.x != 0.f || acc.y != 0.f) {
+      const float2 o = out[k];
+      out[k] = make_float2(o.x + acc.x, o.y + acc.y);
+    }
+  }
+}
+
 int wgs(const Plan& p, int units) {
   const int g = p.persistent_wgs > 0 ? p.persistent_wgs : units;
   return units < g ? (units > 0 ? units : 1) : g;
@@ -400,7 +442,13 @@ int dde_grid(const Plan& p, const int4* units, int nunits, const Item* items, co
 
 int dde_merge(const Plan& p, float2* grid, bool add, hipStream_t s) {
   return dispatch(p, [&]<int T, int H>() -> int {
-    if (add)
+    if (p.windowed && add)
+      hipLaunchKernelGGL((k_dde_merge_win<T, H, true>), dim3(p.n_gtiles), dim3(DT), 0, s, grid, p.dde.patch,
+                         p.dde.tile_has, p.K, p.tpa, p.gta);
+    else if (p.windowed)
+      hipLaunchKernelGGL((k_dde_merge_win<T, H, false>), dim3(p.n_gtiles), dim3(DT), 0, s, grid, p.dde.patch,
+                         p.dde.tile_has, p.K, p.tpa, p.gta);
+    else if (add)
       hipLaunchKernelGGL((k_dde_merge<T, H, true>), dim3(p.n_tiles), dim3(DT), 0, s, grid, p.dde.patch,
                          p.dde.tile_has, p.K, p.tpa);
     else

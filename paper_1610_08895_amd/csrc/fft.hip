@@ -32,6 +32,13 @@ struct ColCfg {
   static constexpr int NT = K <= 512 ? 256 : 512;
 };
 
+// Adjoint column panels of windowed plans: a wavefront or more per four columns.
+template <int K>
+struct WinColCfg {
+  static constexpr int W = 4;
+  static constexpr int NT = W * K / 16 < 64 ? 64 : W * K / 16;
+};
+
 // Column panel of workgroup b of nb: consecutive blocks go round-robin to the eight XCDs,
 // so neighbouring panels, which share 128-byte rows of the grid, are given to blocks on
 // the same XCD (and its L2) when nb is a multiple of 8.
@@ -92,6 +99,44 @@ __global__ __launch_bounds__(NT) void k_adj_cols(const float2* __restrict__ grid
   auto store = [&](int w, int q, float2 v) {
     const int r = pix_of(q, n, K);
     if (r >= 0) rows[size_t(r) * K + c0 + w] = v;
+  };
+  FftPanel<K, W, NT, +1, true>::template run<TwLds<K, W>::fits>(lds, tw, twl, load, store);
+}
+
+// The adjoint column pass of a windowed plan, whose grid comes as the gridding tiles' patches:
+// stored column s holds grid column s - 3 (mod K), so that tile tx's region starts at stored
+// column GSIDE tx, and stored row likewise; a cell in the first 7 rows or columns of its tile
+// also lies in the reach of the tile above, to the left, or both.  All four are loaded for every
+// cell, the absent ones from a cell of the own patch that is always zero: loads under a branch
+// would be waited for one after the other (36 us at K = 1024, against 9.8 so; the pass over a
+// merged grid took 9.2, and the halo pass before it 7.0).
+constexpr int REACH = KB_J - 1;
+constexpr int SHIFT = KB_J / 2 - 1;
+
+template <int K, int W, int NT>
+__global__ __launch_bounds__(NT) void k_adj_cols_win(const float2* __restrict__ patch, float2* __restrict__ rows,
+                                                     const float2* __restrict__ tw) {
+  constexpr int n = K / 2, TA = K / GSIDE;
+  __shared__ float2 lds[K * W];
+  __shared__ float2 twl[TwLds<K, W>::size];
+  const int c0 = panel_of(blockIdx.x, gridDim.x) * W;
+  // the data branch's kernels issue ahead of the sparsity branch's waves sharing their SIMDs
+  __builtin_amdgcn_s_setprio(3);
+  auto load = [&](int w, int k) -> float2 {
+    const int s = c0 + w, sy = (k + SHIFT) & (K - 1);
+    const int tx = s / GSIDE, lx = s % GSIDE, ty = sy / GSIDE, ly = sy % GSIDE;
+    const int tl = (tx - 1) & (TA - 1), tu = (ty - 1) & (TA - 1);
+    const int o = ly * PATCH_W + lx, own = (ty * TA + tx) * PATCH_CELLS, zero = own + PATCH_CELLS - 1;
+    const bool left = lx < REACH, up = ly < REACH;
+    const float2 a = patch[own + o];
+    const float2 b = patch[left ? (ty * TA + tl) * PATCH_CELLS + o + GSIDE : zero];
+    const float2 c = patch[up ? (tu * TA + tx) * PATCH_CELLS + o + GSIDE * PATCH_W : zero];
+    const float2 d = patch[left && up ? (tu * TA + tl) * PATCH_CELLS + o + GSIDE * PATCH_W + GSIDE : zero];
+    return cadd(cadd(a, b), cadd(c, d));
+  };
+  auto store = [&](int w, int q, float2 v) {
+    const int r = pix_of(q, n, K);
+    if (r >= 0) rows[size_t(r) * K + ((c0 + w - SHIFT) & (K - 1))] = v;
   };
   FftPanel<K, W, NT, +1, true>::template run<TwLds<K, W>::fits>(lds, tw, twl, load, store);
 }
@@ -167,9 +212,15 @@ int fwd_cols_impl(const Plan& p, const float*, float2* grid, hipStream_t s) {
 
 template <int K>
 int adj_cols_impl(const Plan& p, const float2* grid, float*, hipStream_t s) {
-  using CC = ColCfg<K>;
-  hipLaunchKernelGGL((k_adj_cols<K, CC::W, CC::NT>), dim3(K / CC::W), dim3(CC::NT), 0, s, grid, p.rowbuf,
-                     p.twiddle);
+  if constexpr (K <= WINDOWED_K) {
+    using WC = WinColCfg<K>;
+    hipLaunchKernelGGL((k_adj_cols_win<K, WC::W, WC::NT>), dim3(K / WC::W), dim3(WC::NT), 0, s, grid, p.rowbuf,
+                       p.twiddle);
+  } else {
+    using CC = ColCfg<K>;
+    hipLaunchKernelGGL((k_adj_cols<K, CC::W, CC::NT>), dim3(K / CC::W), dim3(CC::NT), 0, s, grid, p.rowbuf,
+                       p.twiddle);
+  }
   RI_LAUNCH_CHECK();
   return RI_OK;
 }

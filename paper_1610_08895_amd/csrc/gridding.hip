@@ -23,7 +23,8 @@
 // taps of a visibility are LDS reads.  Block norms are accumulated per item in FP64 and
 // reduced per block by a second kernel in a fixed order (no atomics, deterministic).
 //
-// Gridding is owner-computes per tile: one workgroup accumulates every active item of a
+// Gridding here is for grids above WINDOWED_K cells per axis (window.hip holds the other, and
+// says why the line lies there).  It is owner-computes per tile: one workgroup accumulates every active item of a
 // tile (all blocks) into an LDS copy of the tile and its reach (exact integer LDS atomics
 // per item, see k_grid_tiles), adds the tile interior to the grid with a plain
 // read-modify-write (no other workgroup writes it) and stores the reach outside the
@@ -879,12 +880,13 @@ int grid_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* grid
     RI_TRY(dde_grid(p, p.dde.tunits, p.dde.n_tunits, p.titems, mask, y, nullptr, nullptr, nullptr, false, false, s));
     return dde_merge(p, grid, false, s);
   }
+  if (p.windowed) return win_apply(p, y, mask, grid, s);
   return grid_units<GR_APPLY>(p, true, p.units, p.n_units, p.titems, mask, grid, y, nullptr, nullptr, nullptr,
                               s, true, true);
 }
 
 int grid_all(const Plan& p, const float2* v, float2* grid, hipStream_t s) {
-  if (p.dde.on()) return grid_apply(p, v, nullptr, grid, s);
+  if (p.dde.on() || p.windowed) return grid_apply(p, v, nullptr, grid, s);
   return grid_units<GR_APPLY>(p, true, p.units, p.n_units, p.titems, nullptr, grid, v, nullptr, nullptr,
                               nullptr, s, true, true);
 }
@@ -893,6 +895,7 @@ int grid_project(const Plan& p, const float2* e, float2* v, const float* shrink,
                  hipStream_t s) {
   if (p.dde.on())  // the tiles' patches; grid_halo adds them into the grid
     return dde_grid(p, p.dde.tunits, p.dde.n_tunits, p.titems, mask, nullptr, e, v, shrink, true, false, s);
+  if (p.windowed) return win_project(p, e, v, shrink, mask, grid, s);
   return grid_units<GR_PROJECT>(p, true, p.units, p.n_units, p.titems, mask, grid, nullptr, e, v, shrink, s,
                                 false);
 }
@@ -900,12 +903,14 @@ int grid_project(const Plan& p, const float2* e, float2* v, const float* shrink,
 int grid_project_all(const Plan& p, const float2* r, float2* v, const float* shrink, float2* grid, hipStream_t s,
                      bool zeroed) {
   if (p.dde.on()) return fail(RI_EINVAL, "grid_project_all: the DDE kernels update the running sum instead");
+  if (p.windowed) return win_project_all(p, r, v, shrink, grid, s);
   return grid_units<GR_FRESH>(p, true, p.units, p.n_units, p.titems, nullptr, grid, nullptr, r, v, shrink, s, false,
                               true, zeroed);
 }
 
 int grid_halo(const Plan& p, float2* grid, hipStream_t s) {
   if (p.dde.on()) return dde_merge(p, grid, true, s);
+  if (p.windowed) return RI_OK;  // no rings: the adjoint column pass adds the regions
   switch (p.tile) {
     case 16: launch_halo<16>(p, grid, true, s); break;
     case 32: launch_halo<32>(p, grid, true, s); break;
@@ -920,17 +925,20 @@ int grid_project_block(const Plan& p, int block, const float2* e, float2* v, con
                        hipStream_t s) {
   const int a = p.bunit_off_host[block], b = p.bunit_off_host[block + 1];
   if (p.dde.on()) return dde_grid(p, p.bunits + a, b - a, p.items, nullptr, nullptr, e, v, shrink, true, true, s);
+  if (p.windowed) return win_project_block(p, block, e, v, shrink, grid, s);
   return grid_units<GR_PROJECT>(p, false, p.bunits + a, b - a, p.items, nullptr, grid, nullptr, e, v, shrink, s,
                                 false);
 }
 
 int grid_blocks_begin(const Plan& p, hipStream_t s) {
   if (p.dde.on()) return dde_zero_patches(p, s);
+  if (p.windowed) return RI_OK;
   return zero_c64(p.halo, size_t(p.n_tiles) * ring_cells(p.tile), s);
 }
 
 int grid_blocks_end(const Plan& p, float2* grid, hipStream_t s) {
   if (p.dde.on()) return dde_merge(p, grid, true, s);
+  if (p.windowed) return RI_OK;
   switch (p.tile) {
     case 16: launch_halo<16>(p, grid, false, s); break;
     case 32: launch_halo<32>(p, grid, false, s); break;

@@ -39,7 +39,7 @@ struct ri_pd_s {
   // weights of a weighted l1 prior (b*n*n, the layout of s; null: the plain prior), which
   // make the bound of step 13's clip alpha w_k per coefficient (reweighted SARA)
   float* wts = nullptr;
-  float2* sum = nullptr;   // sum_i M_i^dagger v~_i on the K x K grid
+  float2* sum = nullptr;   // sum_i M_i^dagger v~_i on the grid (Plan::adj_cells)
   double* eps = nullptr;   // d
   double* stats = nullptr; // d x 2
   float* shrink = nullptr;  // d: max(0, 1 - eps_i / ||r_i||) of the current step
@@ -203,7 +203,7 @@ int ri_pd_create(ri_pd* out, ri_plan plan, ri_sara sara, const float* y, const d
   P->sara = &S;
   P->prm = q;
   P->alpha = float(q.kappa * q.psi_norm);
-  const size_t N = size_t(p.n) * p.n, M = size_t(p.M), KK = size_t(p.K) * p.K;
+  const size_t N = size_t(p.n) * p.n, M = size_t(p.M), KK = p.adj_cells();
   int rc = RI_OK;
   auto step = [&](int r) {
     if (rc == RI_OK) rc = r;
@@ -273,13 +273,13 @@ int ri_pd_step(ri_pd P, const uint8_t* mask, double* stats, hipStream_t stream) 
   // blocks' changes are added to it
   const bool fresh = mask == nullptr && !p.dde.on();
   RI_STAGE(P, RI_STAGE_DEGRID, stream,
-           ri::degrid_residual(p, p.grid, P->y, P->v, P->e, mask, stream, fresh ? P->sum : nullptr));
+           ri::degrid_residual(p, p.grid, P->y, P->v, P->e, mask, stream, fresh && !p.windowed ? P->sum : nullptr));
   RI_STAGE(P, RI_STAGE_BLOCK_NORMS, stream, ri::block_stats(p, mask, P->stats, stats, stream, P->eps, P->shrink));
   if (fresh)
     RI_STAGE(P, RI_STAGE_GRID, stream, ri::grid_project_all(p, P->e, P->v, P->shrink, P->sum, stream, true));
   else
     RI_STAGE(P, RI_STAGE_GRID, stream, ri::grid_project(p, P->e, P->v, P->shrink, mask, P->sum, stream));
-  RI_STAGE(P, RI_STAGE_GRID_HALO, stream, ri::grid_halo(p, P->sum, stream));
+  if (!p.windowed || p.dde.on()) RI_STAGE(P, RI_STAGE_GRID_HALO, stream, ri::grid_halo(p, P->sum, stream));
   RI_STAGE(P, RI_STAGE_IFFT_COLS, stream, ri::fft_adjoint_cols(p, P->sum, stream));
   if (fork) {
     RI_HIP(hipStreamWaitEvent(P->side, P->ev_fork, 0));

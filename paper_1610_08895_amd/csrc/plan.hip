@@ -82,9 +82,21 @@ void destroy_plan(Plan& p) {
   dev_free(p.block_tmp);
   dev_free(p.halo);
   dev_free(p.empty_tiles);
+  dev_free(p.gtiles);
+  dev_free(p.woff);
+  dev_free(p.wsegs);
+  dev_free(p.btiles);
+  dev_free(p.patch);
   dev_free(p.norm_tmp);
   dev_free(p.dsum);
   dde_destroy(p.dde);
+}
+
+template <class T>
+int upload(T** dst, const std::vector<T>& src, hipStream_t s) {
+  RI_TRY(dev_alloc(dst, src.size()));
+  if (!src.empty()) RI_HIP(hipMemcpyAsync(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice, s));
+  return RI_OK;
 }
 
 using KV = std::pair<uint64_t, int64_t>;  // (tile << 32 | tile-local cell ly * T + lx, index)
@@ -183,6 +195,7 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
   p.persistent_wgs = tune ? tune->persistent_wgs : 0;
   p.slice_vis = tune && tune->slice_vis != 0 ? tune->slice_vis : -1;
   p.tpa = p.K / p.tile;
+  p.windowed = p.K <= WINDOWED_K;
   p.block_off_host.assign(off, off + d + 1);
 
   // Kaiser-Bessel polynomials
@@ -201,7 +214,7 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
   uint2* packed = nullptr;  // M packed coordinates, user order (device)
   std::vector<uint64_t> skeys;
   std::vector<int> sidx;
-  RI_TRY(plan_sort(uv, M, off, d, K, T, tpa, &packed, skeys, sidx, s));
+  RI_TRY(plan_sort(uv, M, off, d, K, T, tpa, p.windowed, &packed, skeys, sidx, s));
   struct Freer {
     uint2*& q;
     ~Freer() { dev_free(q); }
@@ -209,6 +222,18 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
   p.order_host.resize(M);
   std::vector<std::vector<Item>> block_items(d);
   std::vector<std::vector<uint32_t>> block_pairs(d), block_boxes(d);
+  std::vector<std::vector<int4>> block_segs(d);  // {first position, count, block, window row << 16 | column}
+  // Windowed plans keep the sorted order.  Their degridding items are cut smaller where M would
+  // not give every CU four workgroups (8192 visibilities at 64^2: 14.8 us with items of up to
+  // 1024 and units of 2048, 6.0 with 256 and 256), unless the (block, tile) runs alone may come
+  // near the count of items that the norms' scratch allows.
+  const int wpt = T / WIN;
+  int64_t kbin = p.bin, dunit_vis = DUNIT_VIS;
+  if (p.windowed && int64_t(d) * tpa * tpa <= 32768) {
+    dunit_vis = std::clamp<int64_t>((M / 1024 + 255) / 256 * 256, DUNIT_VIS_MIN, DUNIT_VIS);
+    kbin = std::min(kbin, dunit_vis);
+  }
+  std::atomic<int> items_info{0};
   std::atomic<int> bad{0};
   const unsigned nthreads = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
   auto work = [&](int i) {
@@ -227,20 +252,33 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
       const uint64_t tile = kv[k].first >> 32;
       int64_t e = k;
       while (e < hi - lo && (kv[e].first >> 32) == tile) ++e;
-      for (int64_t a = k; a < e; a += p.bin) {
-        const int64_t w = std::min<int64_t>(p.bin, e - a);
-        // footprint box: the item's smallest and largest tile-local row and column
-        int b[4] = {T, -1, T, -1};
-        for (int64_t m = a; m < a + w; ++m) {
-          const int local = int(uint32_t(kv[m].first)), ly = local / T, lx = local % T;
-          b[0] = std::min(b[0], ly);
-          b[1] = std::max(b[1], ly);
-          b[2] = std::min(b[2], lx);
-          b[3] = std::max(b[3], lx);
+      items_info += int((e - k + p.bin - 1) / p.bin);
+      for (int64_t a = k; a < e; a += kbin) {
+        const int64_t w = std::min<int64_t>(kbin, e - a);
+        if (!p.windowed) {
+          // footprint box: the item's smallest and largest tile-local row and column
+          int b[4] = {T, -1, T, -1};
+          for (int64_t m = a; m < a + w; ++m) {
+            const int local = int(uint32_t(kv[m].first)), ly = local / T, lx = local % T;
+            b[0] = std::min(b[0], ly);
+            b[1] = std::max(b[1], ly);
+            b[2] = std::min(b[2], lx);
+            b[3] = std::max(b[3], lx);
+          }
+          bxs.push_back(uint32_t(b[0]) | uint32_t(b[1]) << 8 | uint32_t(b[2]) << 16 | uint32_t(b[3]) << 24);
+          prs.push_back(item_order(kv.data() + a, w, T));
+        } else {
+          prs.push_back(0);  // no same-cell pairs are placed
         }
-        bxs.push_back(uint32_t(b[0]) | uint32_t(b[1]) << 8 | uint32_t(b[2]) << 16 | uint32_t(b[3]) << 24);
-        prs.push_back(item_order(kv.data() + a, w, T));
         its.push_back(make_int4(i, int(tile), int(lo + a), int(w)));
+      }
+      for (int64_t a = k; p.windowed && a < e;) {  // one segment per window
+        const int sub = int(uint32_t(kv[a].first) >> 6);
+        int64_t z = a + 1;
+        while (z < e && int(uint32_t(kv[z].first) >> 6) == sub) ++z;
+        const int wy = int(tile) / tpa * wpt + sub / wpt, wx = int(tile) % tpa * wpt + sub % wpt;
+        block_segs[i].push_back(make_int4(int(lo + a), int(z - a), i, (wy << 16) | wx));
+        a = z;
       }
       k = e;
     }
@@ -267,6 +305,56 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
   }
   p.item_off_host[d] = int(items.size());
   p.n_items = int(items.size());
+  p.n_items_info = items_info;
+
+  // windowed plans: the gridding tiles, most visibilities first (the dispatcher hands freed
+  // slots the next one, so the longest start first), and their windows' segments, blocks in order
+  std::vector<int> gtiles, woff, btiles;
+  std::vector<int4> wsegs;
+  if (p.windowed) {
+    p.gta = K / GSIDE;
+    p.n_gtiles = p.gta * p.gta;
+    auto slot = [&](const int4& sg) {  // 4 tile + window of the tile
+      const int wy = sg.w >> 16, wx = sg.w & 0xffff;
+      return 4 * ((wy / 2) * p.gta + wx / 2) + (wy % 2) * 2 + wx % 2;
+    };
+    std::vector<int64_t> vis(p.n_gtiles, 0), wvis(4 * size_t(p.n_gtiles), 0);
+    for (const auto& v : block_segs)
+      for (const int4& sg : v) wvis[slot(sg)] += sg.y;
+    for (size_t q = 0; q < wvis.size(); ++q) vis[q / 4] += wvis[q];
+    gtiles.resize(p.n_gtiles);
+    for (int t = 0; t < p.n_gtiles; ++t) gtiles[t] = t;
+    std::stable_sort(gtiles.begin(), gtiles.end(), [&](int a, int b) { return vis[a] > vis[b]; });
+    std::vector<int> pos(p.n_gtiles);
+    for (int u = 0; u < p.n_gtiles; ++u) pos[gtiles[u]] = u;
+    auto bucket = [&](const int4& sg) {
+      const int q = slot(sg);
+      return 4 * size_t(pos[q / 4]) + q % 4;
+    };
+    woff.assign(4 * size_t(p.n_gtiles) + 1, 0);
+    for (const auto& v : block_segs)
+      for (const int4& sg : v) woff[bucket(sg) + 1] += 1;
+    for (size_t q = 0; q + 1 < woff.size(); ++q) woff[q + 1] += woff[q];
+    wsegs.resize(woff.back());
+    std::vector<int> fill(woff.begin(), woff.end() - 1), last(p.n_gtiles, -1);
+    p.btile_off_host.assign(1, 0);
+    for (int i = 0; i < d; ++i) {
+      for (const int4& sg : block_segs[i]) {
+        const size_t q = bucket(sg);
+        wsegs[fill[q]++] = make_int4(sg.x, sg.y, i, 0);
+        if (last[q / 4] != i) {
+          last[q / 4] = i;
+          btiles.push_back(int(q / 4));
+        }
+      }
+      p.btile_off_host.push_back(int(btiles.size()));
+    }
+    // Four wavefronts per window while all of them (16 per tile) come to at most the chip's
+    // 16384 wavefront slots; on larger grids the tiles fill the chip by themselves and the
+    // split only adds empty wavefronts.  Per launch with 1, 2 and 4: 12.2, 9.1, 8.5 us at 64^2
+    // (64 tiles), 24.4, 17.8, 16.1 at 256^2 (1024), 25.9, 26.8, 57.3 at 512^2 (4096).
+    p.win_split = p.n_gtiles <= 1024 ? 4 : 1;
+  }
 
   // items grouped by tile, and tiles grouped into the four gridding colours
   p.n_tiles = tpa * tpa;
@@ -291,6 +379,11 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
     for (int t : ts) units.push_back(make_int4(t, tile_cnt[t], tile_cnt[t + 1], tile_vis[t]));
   }
   p.tile_units_host = units;
+  if (p.windowed) {  // none of what follows but the degridding units
+    units.clear();
+    empty_tiles.clear();
+    p.n_empty = 0;
+  }
   // split dense tiles into slices of whole items
   std::vector<int> unit_patch;
   std::vector<std::vector<int>> tile_patches(p.n_tiles);
@@ -344,11 +437,11 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
   }
   p.n_units = int(units.size());
   std::vector<int4> dunits;
-  for (const int4& un : units) {
+  for (const int4& un : p.windowed ? p.tile_units_host : units) {
     int a = un.y, acc = 0;
     for (int q = un.y; q < un.z; ++q) {
       const int w = items[tile_items[q]].w;
-      if (q > a && acc + w > DUNIT_VIS) {
+      if (q > a && acc + w > dunit_vis) {
         dunits.push_back(make_int4(un.x, a, q, acc));
         a = q;
         acc = 0;
@@ -407,56 +500,41 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
   for (int r = 0; r < n; ++r) sc[r] = float(1.0 / kb_hat(double(r - n / 2) / K, J, p.beta));
 
   RI_TRY(dev_alloc(&p.coord, M));
-  RI_TRY(dev_alloc(&p.order, M));
-  RI_TRY(dev_alloc(&p.items, items.size()));
-  RI_TRY(dev_alloc(&p.item_box, items.size()));
-  RI_TRY(dev_alloc(&p.item_pairs, items.size()));
-  RI_TRY(dev_alloc(&p.item_off, d + 1));
-  RI_TRY(dev_alloc(&p.block_off, d + 1));
-  RI_TRY(dev_alloc(&p.twiddle, K));
-  RI_TRY(dev_alloc(&p.scale, n));
+  RI_TRY(upload(&p.order, p.order_host, s));
+  RI_TRY(plan_gather_coord(packed, p.order, M, p.coord, s));
+  RI_TRY(upload(&p.items, items_dev, s));
+  RI_TRY(upload(&p.titems, titems, s));
+  RI_TRY(upload(&p.item_box, item_box, s));
+  RI_TRY(upload(&p.item_pairs, item_pairs, s));
+  RI_TRY(upload(&p.item_off, p.item_off_host, s));
+  RI_TRY(upload(&p.block_off, p.block_off_host, s));
+  RI_TRY(upload(&p.twiddle, tw, s));
+  RI_TRY(upload(&p.scale, sc, s));
+  RI_TRY(upload(&p.units, units, s));
+  RI_TRY(upload(&p.bunits, bunits, s));
+  RI_TRY(upload(&p.dunits, dunits, s));
+  RI_TRY(upload(&p.unit_patch, unit_patch, s));
+  RI_TRY(upload(&p.tile_sp_off, tile_sp_off, s));
+  RI_TRY(upload(&p.tile_sp, tile_sp, s));
+  RI_TRY(upload(&p.empty_tiles, empty_tiles, s));
+  RI_TRY(upload(&p.gtiles, gtiles, s));
+  RI_TRY(upload(&p.woff, woff, s));
+  RI_TRY(upload(&p.wsegs, wsegs, s));
+  RI_TRY(upload(&p.btiles, btiles, s));
   RI_TRY(dev_alloc(&p.grid, size_t(K) * K));
   RI_TRY(dev_alloc(&p.rowbuf, size_t(n) * K));
-  RI_TRY(dev_alloc(&p.titems, items.size()));
-  RI_TRY(dev_alloc(&p.units, units.size()));
-  RI_TRY(dev_alloc(&p.bunits, bunits.size()));
-  RI_TRY(dev_alloc(&p.dunits, dunits.size()));
-  RI_TRY(dev_alloc(&p.unit_patch, unit_patch.size()));
-  RI_TRY(dev_alloc(&p.tile_sp_off, tile_sp_off.size()));
-  if (p.n_spatch > 0) {
-    RI_TRY(dev_alloc(&p.tile_sp, tile_sp.size()));
-    RI_TRY(dev_alloc(&p.spatch, size_t(p.n_spatch) * (p.tile + 8) * (p.tile + 8)));
-  }
+  if (p.n_spatch > 0) RI_TRY(dev_alloc(&p.spatch, size_t(p.n_spatch) * (p.tile + 8) * (p.tile + 8)));
   RI_TRY(dev_alloc(&p.item_part, 2 * size_t(PART_WAVES) * items.size()));
   RI_TRY(dev_alloc(&p.block_tmp, 2 * size_t(d)));
-  RI_TRY(dev_alloc(&p.halo, size_t(p.n_tiles) * ring_cells(p.tile)));
-  if (p.n_empty > 0) {
-    RI_TRY(dev_alloc(&p.empty_tiles, empty_tiles.size()));
-    RI_HIP(hipMemcpyAsync(p.empty_tiles, empty_tiles.data(), empty_tiles.size() * sizeof(int), hipMemcpyHostToDevice,
-                          s));
-  }
   RI_TRY(dev_alloc(&p.norm_tmp, size_t(n) * n));
   RI_TRY(dev_alloc(&p.dsum, SUMSQ_SCRATCH));
-  RI_HIP(hipMemcpyAsync(p.order, p.order_host.data(), M * sizeof(int), hipMemcpyHostToDevice, s));
-  RI_TRY(plan_gather_coord(packed, p.order, M, p.coord, s));
-  RI_HIP(hipMemcpyAsync(p.items, items_dev.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.titems, titems.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.item_box, item_box.data(), items.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.item_pairs, item_pairs.data(), items.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.item_off, p.item_off_host.data(), (d + 1) * sizeof(int), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.block_off, p.block_off_host.data(), (d + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.twiddle, tw.data(), K * sizeof(float2), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.units, units.data(), units.size() * sizeof(int4), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.bunits, bunits.data(), bunits.size() * sizeof(int4), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.dunits, dunits.data(), dunits.size() * sizeof(int4), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.unit_patch, unit_patch.data(), unit_patch.size() * sizeof(int), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.tile_sp_off, tile_sp_off.data(), tile_sp_off.size() * sizeof(int), hipMemcpyHostToDevice,
-                        s));
-  if (p.n_spatch > 0)
-    RI_HIP(hipMemcpyAsync(p.tile_sp, tile_sp.data(), tile_sp.size() * sizeof(int), hipMemcpyHostToDevice, s));
-  RI_HIP(hipMemcpyAsync(p.scale, sc.data(), n * sizeof(float), hipMemcpyHostToDevice, s));
-  // tiles without visibilities keep an all-zero halo patch forever
-  RI_TRY(zero_c64(p.halo, size_t(p.n_tiles) * ring_cells(p.tile), s));
+  if (p.windowed) {
+    RI_TRY(dev_alloc(&p.patch, p.adj_cells()));
+  } else {
+    // tiles without visibilities keep an all-zero halo patch forever
+    RI_TRY(dev_alloc(&p.halo, size_t(p.n_tiles) * ring_cells(p.tile)));
+    RI_TRY(zero_c64(p.halo, size_t(p.n_tiles) * ring_cells(p.tile), s));
+  }
   RI_HIP(hipStreamSynchronize(s));
   return RI_OK;
 }
@@ -469,8 +547,8 @@ int phi_apply(const Plan& p, const float* x, float* y, const uint8_t* mask, hipS
 }
 
 int phi_adj_apply(const Plan& p, const float* y, float* x, const uint8_t* mask, hipStream_t s) {
-  RI_TRY(grid_apply(p, reinterpret_cast<const float2*>(y), mask, p.grid, s));
-  return fft_adjoint(p, p.grid, x, s);
+  RI_TRY(grid_apply(p, reinterpret_cast<const float2*>(y), mask, p.adj_buffer(), s));
+  return fft_adjoint(p, p.adj_buffer(), x, s);
 }
 
 }  // namespace ri
@@ -513,7 +591,7 @@ int ri_plan_info(ri_plan plan, int* n, int64_t* M, int* d, int* K, int* tile, in
   if (d) *d = plan->p.d;
   if (K) *K = plan->p.K;
   if (tile) *tile = plan->p.tile;
-  if (n_items) *n_items = plan->p.n_items;
+  if (n_items) *n_items = plan->p.n_items_info;
   return RI_OK;
 }
 

@@ -56,6 +56,18 @@ constexpr int GRID_LANES = 256;  // threads per workgroup of the tile gridding
 constexpr int TILE_PAD = 9;
 constexpr int DUNIT_VIS = 2048;  // visibilities per degridding unit (several items of one tile)
 constexpr int PART_WAVES = 4;    // FP64 norm partials per work item (one per wavefront)
+constexpr int DUNIT_VIS_MIN = 256;
+
+// Windowed plans (window.hip), for grids of up to WINDOWED_K cells per axis: windows of WIN x
+// WIN cells; GSIDE x GSIDE cells (2 x 2 windows) make a gridding tile, whose gridded region
+// (tile and reach, 23 x 23 cells starting KB_J / 2 - 1 cells before the tile) is stored in a
+// slot of PATCH_W x PATCH_W (the last row and column stay zero).  The grid of the adjoint
+// exists as these patches only: a cell's value is the sum over the regions that cover it.
+constexpr int WINDOWED_K = 1024;
+constexpr int WIN = 8;
+constexpr int GSIDE = 16;
+constexpr int PATCH_W = 24;
+constexpr int PATCH_CELLS = PATCH_W * PATCH_W;
 // Cells of a tile's halo ring: its (tile + 8)^2 region (the tile and the kernel's reach)
 // less the tile itself.
 constexpr int ring_cells(int tile) { return (tile + 8) * (tile + 8) - tile * tile; }
@@ -86,6 +98,20 @@ struct Plan {
   int slice_vis = -1;  // <= 0: tiles are never split
   KBPoly poly{};
   double poly_err = 0.0;
+
+  bool windowed = false;
+  int n_items_info = 0;             // items of at most `bin` visibilities, as ri_plan_info counts them
+  int win_split = 1;                // wavefronts per window (1 or 4)
+  int gta = 0, n_gtiles = 0;        // gridding tiles per axis and in all
+  int* gtiles = nullptr;            // n_gtiles tile indices, most visibilities first
+  int* woff = nullptr;              // 4 n_gtiles + 1: ranges of wsegs, by tile (in that order) and window
+  int4* wsegs = nullptr;            // segments {first position, count, block, 0}
+  int* btiles = nullptr;            // positions in gtiles, by block
+  std::vector<int> btile_off_host;  // d + 1
+  float2* patch = nullptr;          // n_gtiles * PATCH_CELLS: the adjoint's work patches
+  // cells of the adjoint's grid as the plan stores it
+  size_t adj_cells() const { return windowed ? size_t(n_gtiles) * PATCH_CELLS : size_t(K) * K; }
+  float2* adj_buffer() const { return windowed ? patch : grid; }
 
   std::vector<int> item_off_host;  // d + 1
   int n_tiles = 0;                  // tpa * tpa
@@ -141,7 +167,7 @@ struct Plan {
 // ---- launchers implemented in fft.hip ----
 // grid = F Z S x (x: n*n real).
 int fft_forward(const Plan& p, const float* x, float2* grid, hipStream_t s);
-// x = Re S Z^dagger F^dagger grid (x: n*n real).
+// x = Re S Z^dagger F^dagger grid (x: n*n real; grid: adj_cells() cells, as everywhere below).
 int fft_adjoint(const Plan& p, const float2* grid, float* x, hipStream_t s);
 // The two passes of each, through the plan's n x K row buffer.
 int fft_forward_rows(const Plan& p, const float* x, hipStream_t s);
@@ -209,13 +235,22 @@ int grid_blocks_end(const Plan& p, float2* grid, hipStream_t s);
 // grid = G^dagger v over all items (rebuilds the running sum from scratch).
 int grid_all(const Plan& p, const float2* v, float2* grid, hipStream_t s);
 
+// ---- window.hip: the gridding of windowed plans ----
+int win_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* patch, hipStream_t s);
+int win_project(const Plan& p, const float2* e, float2* v, const float* shrink, const uint8_t* mask, float2* patch,
+                hipStream_t s);
+int win_project_all(const Plan& p, const float2* r, float2* v, const float* shrink, float2* patch, hipStream_t s);
+int win_project_block(const Plan& p, int block, const float2* e, float2* v, const float* shrink, float2* patch,
+                      hipStream_t s);
+
 // ---- plan creation on the device (plan_sort.hip) ----
 // Packs the M coordinates (uv host, user order) into *packed (device, allocated here, the
-// caller frees it) and sorts the visibilities by (block, tile, cell in the tile), stably;
-// keys_sorted / idx_sorted receive the sorted keys (block << 28 | tile << 12 | cell) and
-// the user index of each sorted position.  Synchronises s.
-int plan_sort(const float* uv, int64_t M, const int64_t* off, int d, int K, int T, int tpa, uint2** packed,
-              std::vector<uint64_t>& keys_sorted, std::vector<int>& idx_sorted, hipStream_t s);
+// caller frees it) and sorts the visibilities by (block, tile, cell in the tile), stably; with
+// windowed, the cells of a tile window by window.  keys_sorted / idx_sorted receive the sorted
+// keys (block << 28 | tile << 12 | cell, or window << 6 | cell of the window) and the user
+// index of each sorted position.  Synchronises s.
+int plan_sort(const float* uv, int64_t M, const int64_t* off, int d, int K, int T, int tpa, bool windowed,
+              uint2** packed, std::vector<uint64_t>& keys_sorted, std::vector<int>& idx_sorted, hipStream_t s);
 // coord[k] = packed[order[k]] (device arrays of M).
 int plan_gather_coord(const uint2* packed, const int* order, int64_t M, uint2* coord, hipStream_t s);
 
@@ -226,7 +261,7 @@ int dde_degrid(const Plan& p, const int4* units, int nunits, const Item* items, 
 int dde_grid(const Plan& p, const int4* units, int nunits, const Item* items, const uint8_t* mask,
              const float2* y, const float2* e, float2* v, const float* shrink, bool project, bool add_patch,
              hipStream_t s);
-// grid (=, or += with add) the sum of the patches covering each cell
+// grid (=, or += with add) the sum of the DDE tiles' patches covering each cell
 int dde_merge(const Plan& p, float2* grid, bool add, hipStream_t s);
 int dde_zero_patches(const Plan& p, hipStream_t s);
 void dde_destroy(Dde& dd);

@@ -35,7 +35,7 @@ __device__ uint32_t pack_coord(float u, double to_cells, int K) {
 
 __global__ __launch_bounds__(256) void k_plan_keys(const float* __restrict__ uv, int64_t M,
                                                    const int64_t* __restrict__ off, int d, int K, int T, int tpa,
-                                                   double to_cells, uint2* __restrict__ packed,
+                                                   double to_cells, int windowed, uint2* __restrict__ packed,
                                                    uint64_t* __restrict__ keys, int* __restrict__ idx) {
   for (int64_t m = int64_t(blockIdx.x) * 256 + threadIdx.x; m < M; m += int64_t(gridDim.x) * 256) {
     int lo = 0, hi = d;  // the block b with off[b] <= m < off[b + 1]
@@ -47,7 +47,10 @@ __global__ __launch_bounds__(256) void k_plan_keys(const float* __restrict__ uv,
     const uint32_t cx = pack_coord(uv[2 * m], to_cells, K), cy = pack_coord(uv[2 * m + 1], to_cells, K);
     packed[m] = make_uint2(cx, cy);
     const uint32_t gx = cx >> FRAC_BITS, gy = cy >> FRAC_BITS;
-    const uint64_t tile = uint64_t(gy / T) * tpa + gx / T, local = uint64_t(gy % T) * T + gx % T;
+    const uint64_t tile = uint64_t(gy / T) * tpa + gx / T;
+    const unsigned ly = gy % T, lx = gx % T;
+    const uint64_t local = windowed ? ((ly / WIN) * (T / WIN) + lx / WIN) * (WIN * WIN) + (ly % WIN) * WIN + lx % WIN
+                                    : ly * T + lx;
     keys[m] = (uint64_t(lo) << 28) | (tile << 12) | local;
     idx[m] = int(m);
   }
@@ -64,8 +67,8 @@ unsigned grid_of(int64_t M) { return unsigned(std::min<int64_t>((M + 255) / 256,
 
 }  // namespace
 
-int plan_sort(const float* uv, int64_t M, const int64_t* off, int d, int K, int T, int tpa, uint2** packed,
-              std::vector<uint64_t>& keys_sorted, std::vector<int>& idx_sorted, hipStream_t s) {
+int plan_sort(const float* uv, int64_t M, const int64_t* off, int d, int K, int T, int tpa, bool windowed,
+              uint2** packed, std::vector<uint64_t>& keys_sorted, std::vector<int>& idx_sorted, hipStream_t s) {
   if (d > (1 << 12) || int64_t(tpa) * tpa > (1 << 16) || T * T > (1 << 12))
     return fail(RI_EINVAL, "plan sort keys: d=%d, %d tiles, tile %d out of range", d, tpa * tpa, T);
   float* d_uv = nullptr;
@@ -87,7 +90,7 @@ int plan_sort(const float* uv, int64_t M, const int64_t* off, int d, int K, int 
     RI_HIP(hipMemcpyAsync(d_uv, uv, size_t(2 * M) * sizeof(float), hipMemcpyHostToDevice, s));
     RI_HIP(hipMemcpyAsync(d_off, off, size_t(d + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_plan_keys, dim3(grid_of(M)), dim3(256), 0, s, d_uv, M, d_off, d, K, T, tpa,
-                       double(K) / (2.0 * M_PI), *packed, k_in, v_in);
+                       double(K) / (2.0 * M_PI), windowed ? 1 : 0, *packed, k_in, v_in);
     RI_LAUNCH_CHECK();
     RI_HIP(hipcub::DeviceRadixSort::SortPairs(nullptr, temp_bytes, k_in, k_out, v_in, v_out, int(M), 0, KEY_BITS,
                                               s));

@@ -1,0 +1,295 @@
+// Gridding by windows, for plans with grids of up to WINDOWED_K cells per axis (gridding.hip
+// holds the kernel for larger grids, and the degridding of both): G_i^dagger with the dual
+// update of step 8 fused in, as in gridding.hip.
+//
+// A window is an aligned 8 x 8 group of grid cells; the footprints of all visibilities whose
+// cell lies in it fall in one 16 x 16 patch of the grid (15 x 15 of it), so with wx_m and wy_m
+// the 8 weights of visibility m placed at its cell's offset in a zero row of 16,
+//
+//   patch[i][j] += sum_m wy_m[i] (v_m wx_m[j])      (rows x visibilities x columns),
+//
+// an FP32 matrix product on the matrix cores (v_mfma_f32_16x16x4_f32, exact FP32
+// multiply-adds).  The placed weight rows pass through a per-wavefront LDS buffer: 64 lanes
+// evaluate the x and the y weights of 32 visibilities (a chunk) at once, store them as columns
+// of a [row][visibility] array over zeros, and read them back in the operands' layouts.  The
+// plan sorts a block's visibilities by tile and window, so that the visibilities of a window
+// are one contiguous run (a segment) per block.
+//
+// Why only small grids: the matrix product takes 16 cycles of a SIMD's matrix unit per
+// visibility, the placing and the loads as much again on the VALU and the LDS, and together
+// they are no faster than gridding.hip's 64 atomics per visibility on a chip that those keep
+// full (2^22 visibilities at 1024^2: 98 us here, 92 us there).  But a 32 x 32 tile per
+// workgroup leaves most of the chip idle on a small grid and its densest tile decides the time;
+// a window per wavefront or less spreads the same work over 16 times as many.  Per launch, tiles
+// with their halo pass -> windows: 2^13 visibilities at 64^2 25.3 -> 8.5 us, 82000 of 327680
+// (masked) at 256^2 46 -> 16.1, 500000 of 10^6 (masked) at 512^2 66 -> 25.9, 1.5 10^6 at 512^2
+// 92.9 -> 35.6; the error of Phi^dagger at the last 1.9e-6 -> 4.5e-7.
+#include <algorithm>
+
+#include "plan.hpp"
+
+namespace ri {
+
+namespace {
+
+constexpr int CH = 32;  // visibilities per chunk: two lanes each (one per axis, or per component)
+// Row pitch of a chunk's weight array in LDS: the 16-byte reads of 16 rows touch every bank
+// equally often.
+constexpr int WP = CH + 4;
+constexpr int WROWS = 16;
+constexpr int WBUF = 2 * WROWS * WP;  // x rows, then y rows
+
+using f32x4 = float __attribute__((ext_vector_type(4)));
+
+// Orders LDS traffic of one wavefront (whose LDS operations execute in program order): the
+// compiler may not move accesses across it, and no instruction is emitted.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Takes over a value loaded ahead, as a move that the compiler cannot merge or delay: the
+// register the value was loaded into is then free for the next load, which would otherwise go
+// to a fresh one and be waited for at once to be copied.
+template <class T>
+__device__ __forceinline__ T take(T x) {
+  T r;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+
+// Lanes of a chunk: lane l = 16 g + m holds component (or axis) g & 1 of visibility
+// 16 (g >> 1) + m.
+__device__ __forceinline__ int lane_vis(int lane) { return ((lane >> 5) << 4) | (lane & 15); }
+
+// Places the weights of this lane's packed coordinate in the chunk's array `w` (x rows, then y
+// rows) as a column over zeros.
+__device__ __forceinline__ void place_weights(float* w, int lane, unsigned packed, const KBPoly& P) {
+  float k[KB_J];
+  int cell;
+  kb_weights(packed, P, k, cell);
+  f32x4* z = reinterpret_cast<f32x4*>(w);
+#pragma unroll
+  for (int i = 0; i < WBUF / 4; i += 64)
+    if (i + 64 <= WBUF / 4 || lane < WBUF / 4 - i) z[i + lane] = f32x4{0.f, 0.f, 0.f, 0.f};
+  wave_lds_fence();
+  float* col = w + ((lane >> 4) & 1) * (WROWS * WP) + (cell & (WIN - 1)) * WP + lane_vis(lane);
+#pragma unroll
+  for (int j = 0; j < KB_J; ++j) col[j * WP] = k[j];
+}
+
+__device__ __forceinline__ f32x4 mfma(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// APPLY: grid y.  PROJECT: step 8 from r and v_old, grid v_new - v_old.  FRESH: every block
+// active, step 8 from r alone, grid v_new.
+enum { GR_APPLY = 0, GR_PROJECT = 1, GR_FRESH = 2 };
+
+// Inclusive prefix sum over the 64 lanes (all active).
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return v;
+}
+
+// One workgroup per tile of 16 x 16 cells, SPLIT wavefronts per window of it, which take the
+// window's chunks in turn.  A wavefront goes through its window's segments (all blocks; those of inactive blocks and, with
+// only >= 0, of other blocks count as empty) in batches of 64, one lane per segment: the
+// prefix sums of their counts go to a table in LDS, in which each lane of a chunk then finds
+// its visibility by bisection.  The patch stays in the matrix accumulators until the window is
+// done; the wavefronts' patches are then summed into the tile's 23 x 23 region and stored in
+// the tile's own slot of the patch array (added to it with `add`), which nobody else writes:
+// no atomics and no order dependence, so results are deterministic.  The adjoint column pass
+// adds the overlapping regions.
+template <int MODE, int SPLIT>
+__global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restrict__ tiles, const int* __restrict__ list, int nlist,
+                                                                 const int* __restrict__ woff, const int4* __restrict__ wsegs,
+                                                                 const uint8_t* __restrict__ mask, int only,
+                                                                 const unsigned* __restrict__ coord, float2* __restrict__ patch, KBPoly P,
+                                                                 const float* __restrict__ y, const float* __restrict__ e,
+                                                                 float* __restrict__ v, const float* __restrict__ shrink, int add) {
+  // the data branch's kernels issue ahead of the sparsity branch's waves sharing their SIMDs
+  __builtin_amdgcn_s_setprio(3);
+  constexpr int NW = 4 * SPLIT, GT = 64 * NW;
+  constexpr int DP = WROWS + 1;  // pitch of a window's patch in LDS
+  static_assert(WROWS * DP * 2 <= WBUF, "a window's patch takes the place of its weights");
+  __shared__ __align__(16) float wbuf[NW][WBUF];
+  __shared__ __align__(16) float vbuf[NW][2 * CH];
+  __shared__ int4 tab[NW][64];
+  __shared__ int touched[NW];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, m = lane & 15, comp = g & 1, sl = lane_vis(lane);
+  float* w = wbuf[wv];
+  for (int b = blockIdx.x; b < nlist; b += gridDim.x) {
+    const int u = list != nullptr ? list[b] : b;
+    const int win = wv / SPLIT, first = (wv % SPLIT) * CH;
+    const int s0 = woff[4 * u + win], s1 = woff[4 * u + win + 1];
+    f32x4 dr = {0.f, 0.f, 0.f, 0.f}, di = {0.f, 0.f, 0.f, 0.f};
+    bool any = false;
+    for (int b0 = s0; b0 < s1; b0 += 64) {
+      const int nb = min(64, s1 - b0);
+      int4 sg = make_int4(0, 0, 0, 0);
+      if (lane < nb) sg = wsegs[b0 + lane];
+      bool act = lane < nb;
+      if (act && mask != nullptr) act = mask[sg.z] != 0;
+      if (only >= 0) act = act && sg.z == only;
+      const int cnt = act ? sg.y : 0;
+      float sh = 0.f;
+      if (MODE != GR_APPLY && act) sh = shrink[sg.z];
+      const int incl = wave_scan(cnt);
+      const int total = __builtin_amdgcn_readlane(incl, 63);
+      if (total == 0) continue;
+      any = true;
+      wave_lds_fence();
+      tab[wv][lane] = make_int4(incl - cnt, sg.x, __float_as_int(sh), sg.w);
+      wave_lds_fence();
+      int step0 = 0;  // the largest power of two below nb
+      if (nb > 1) step0 = 1 << (31 - __builtin_clz(nb - 1));
+      // this lane's operands of the chunk at q (of the batch's last visibility past its end)
+      unsigned cn;
+      float rn, on = 0.f, shn = 0.f;
+      int pn;
+      auto load_vis = [&](int q) {
+        const int s = min(q + sl, total - 1);
+        int k = 0;
+        for (int st = step0; st > 0; st >>= 1)
+          if (tab[wv][k + st].x <= s) k += st;
+        const int4 en = tab[wv][k];
+        pn = en.y + s - en.x;
+        shn = __int_as_float(en.z);
+        const size_t i = 2 * size_t(pn) + comp;
+        cn = coord[i];
+        if (MODE == GR_APPLY) {
+          rn = y[i];
+        } else {
+          rn = e[i];
+          if (MODE == GR_PROJECT) on = v[i];
+        }
+      };
+      load_vis(first);
+      for (int q = first; q < total; q += SPLIT * CH) {
+        const unsigned cw = take(cn);
+        const int pos = pn;
+        const float old = MODE == GR_PROJECT ? take(on) : 0.f;
+        float val = take(rn);
+        if (MODE != GR_APPLY) val *= shn;
+        __builtin_amdgcn_sched_barrier(0);
+        load_vis(q + SPLIT * CH);
+        const bool in = q + sl < total;
+        if (MODE != GR_APPLY && in) v[2 * size_t(pos) + comp] = val;
+        if (MODE == GR_PROJECT) val -= old;
+        if (!in) val = 0.f;
+        if (__ballot(val != 0.f) == 0ull) continue;  // duals that did not change
+        wave_lds_fence();
+        place_weights(w, lane, cw, P);
+        vbuf[wv][comp * CH + sl] = val;
+        wave_lds_fence();
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          if (t > 0 && q + 16 * t >= total) continue;
+          const int o = 16 * t + 4 * g;
+          const f32x4 a = *reinterpret_cast<const f32x4*>(w + (WROWS + m) * WP + o);
+          const f32x4 x = *reinterpret_cast<const f32x4*>(w + m * WP + o);
+          const f32x4 vr = *reinterpret_cast<const f32x4*>(&vbuf[wv][o]);
+          const f32x4 vi = *reinterpret_cast<const f32x4*>(&vbuf[wv][CH + o]);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            dr = mfma(a[k], x[k] * vr[k], dr);
+            di = mfma(a[k], x[k] * vi[k], di);
+          }
+        }
+      }
+    }
+    // the window's patch, rows 4 g + k and column m in this lane, to LDS
+    wave_lds_fence();
+    float2* d = reinterpret_cast<float2*>(w);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) d[(4 * g + k) * DP + m] = make_float2(dr[k], di[k]);
+    if (lane == 0) touched[wv] = any;
+    __syncthreads();
+    bool changed = !add;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) changed = changed || touched[k] != 0;
+    if (changed) {
+      float2* pt = patch + size_t(tiles[u]) * PATCH_CELLS;
+      for (int c = threadIdx.x; c < PATCH_CELLS; c += GT) {
+        const int R = c / PATCH_W, C = c - (c / PATCH_W) * PATCH_W;
+        float2 s = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int wy = 0; wy < 2; ++wy)
+#pragma unroll
+          for (int wx = 0; wx < 2; ++wx) {
+            const int r = R - WIN * wy, cc = C - WIN * wx;
+            if (r >= 0 && r < WROWS && cc >= 0 && cc < WROWS) {
+#pragma unroll
+              for (int k = 0; k < SPLIT; ++k) {
+                const float2 t = reinterpret_cast<const float2*>(wbuf[(2 * wy + wx) * SPLIT + k])[r * DP + cc];
+                s.x += t.x;
+                s.y += t.y;
+              }
+            }
+          }
+        if (!add) {
+          pt[c] = s;
+        } else if (s.x != 0.f || s.y != 0.f) {
+          const float2 old = pt[c];
+          pt[c] = make_float2(old.x + s.x, old.y + s.y);
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+const float* words(const float2* p) { return reinterpret_cast<const float*>(p); }
+float* words(float2* p) { return reinterpret_cast<float*>(p); }
+
+template <int MODE, int SPLIT>
+int launch(const Plan& p, const int* list, int nlist, const uint8_t* mask, int only, float2* patch, const float2* y,
+           const float2* e, float2* v, const float* shrink, bool add, hipStream_t s) {
+  const int g = p.persistent_wgs > 0 ? std::min(p.persistent_wgs, nlist) : nlist;
+  hipLaunchKernelGGL((k_win_grid<MODE, SPLIT>), dim3(g), dim3(256 * SPLIT), 0, s, p.gtiles, list, nlist, p.woff,
+                     p.wsegs, mask, only, reinterpret_cast<const unsigned*>(p.coord), patch, p.poly, words(y),
+                     words(e), words(v), shrink, add ? 1 : 0);
+  RI_LAUNCH_CHECK();
+  return RI_OK;
+}
+
+// Over the tiles listed (null: every tile, densest first; tiles without visibilities are among
+// them, so that a fresh pass also clears what the DDE kernels may have left there).
+template <int MODE>
+int grid_tiles(const Plan& p, const int* list, int nlist, const uint8_t* mask, int only, float2* patch,
+               const float2* y, const float2* e, float2* v, const float* shrink, bool add, hipStream_t s) {
+  if (nlist <= 0) return RI_OK;
+  return p.win_split == 1 ? launch<MODE, 1>(p, list, nlist, mask, only, patch, y, e, v, shrink, add, s)
+                          : launch<MODE, 4>(p, list, nlist, mask, only, patch, y, e, v, shrink, add, s);
+}
+
+}  // namespace
+
+int win_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* patch, hipStream_t s) {
+  return grid_tiles<GR_APPLY>(p, nullptr, p.n_gtiles, mask, -1, patch, y, nullptr, nullptr, nullptr, false, s);
+}
+
+int win_project(const Plan& p, const float2* e, float2* v, const float* shrink, const uint8_t* mask, float2* patch,
+                hipStream_t s) {
+  return grid_tiles<GR_PROJECT>(p, nullptr, p.n_gtiles, mask, -1, patch, nullptr, e, v, shrink, true, s);
+}
+
+int win_project_all(const Plan& p, const float2* r, float2* v, const float* shrink, float2* patch, hipStream_t s) {
+  return grid_tiles<GR_FRESH>(p, nullptr, p.n_gtiles, nullptr, -1, patch, nullptr, r, v, shrink, false, s);
+}
+
+int win_project_block(const Plan& p, int block, const float2* e, float2* v, const float* shrink, float2* patch,
+                      hipStream_t s) {
+  const int a = p.btile_off_host[block], b = p.btile_off_host[block + 1];
+  return grid_tiles<GR_PROJECT>(p, p.btiles + a, b - a, nullptr, block, patch, nullptr, e, v, shrink, true, s);
+}
+
+}  // namespace ri
