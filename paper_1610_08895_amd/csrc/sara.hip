@@ -12,7 +12,7 @@
 // s = clip(s + Psi^dagger x~, -alpha, alpha), is applied as each coefficient is produced,
 // with the old coefficients loaded before the input is staged; for the weighted l1 prior of
 // reweighted SARA the bound is alpha w_k, with the weights w laid out like s.  The last
-// synthesis level sums all bases in registers.
+// synthesis level sums all bases.
 #include <cmath>
 #include <new>
 #include <vector>
@@ -72,7 +72,7 @@ __device__ __forceinline__ void put_coef(const DwtArgs& A, size_t k, float v) {
 // tile (i0, j0) of each subband.  Sizes are powers of two, so indices wrap with masks.
 template <int L>
 __device__ __forceinline__ void analysis_tile(const DwtArgs& A, const float* __restrict__ hw, int w, int i0,
-                                              int j0, float* in, float* lo, float* hi) {
+                                              int j0, float* in, float2* lh) {
   const float* __restrict__ gw = hw + MAX_TAPS;
   constexpr int RE = 2 * TO + L - 2;       // input rows / columns the tile reads
   constexpr int RW = 2 * TO + MAX_TAPS - 2; // LDS row stride
@@ -105,31 +105,33 @@ __device__ __forceinline__ void analysis_tile(const DwtArgs& A, const float* __r
   __syncthreads();
   for (int idx = threadIdx.x; idx < RE * TO; idx += ST) {
     const int rho = idx / TO, j = idx - rho * TO;
-    const float* row = &in[rho * RW + 2 * j];
+    const float2* row = reinterpret_cast<const float2*>(&in[rho * RW + 2 * j]);
     float a = 0.f, d = 0.f;
 #pragma unroll
-    for (int t = 0; t < L; ++t) {
-      a = fmaf(hw[t], row[t], a);
-      d = fmaf(gw[t], row[t], d);
+    for (int t = 0; t < L / 2; ++t) {
+      const float2 v = row[t];
+      a = fmaf(hw[2 * t], v.x, a);
+      d = fmaf(gw[2 * t], v.x, d);
+      a = fmaf(hw[2 * t + 1], v.y, a);
+      d = fmaf(gw[2 * t + 1], v.y, d);
     }
-    lo[rho * TO + j] = a;
-    hi[rho * TO + j] = d;
+    lh[rho * TO + j] = make_float2(a, d);
   }
   __syncthreads();
   if (!mine) return;
-  float ll = 0.f, lh = 0.f, hl = 0.f, hh = 0.f;
+  float ll = 0.f, hi = 0.f, hl = 0.f, hh = 0.f;  // hi: low along y, high along x
 #pragma unroll
   for (int t = 0; t < L; ++t) {
-    const float l = lo[(2 * pi + t) * TO + pj], h = hi[(2 * pi + t) * TO + pj];
-    ll = fmaf(hw[t], l, ll);
-    lh = fmaf(hw[t], h, lh);
-    hl = fmaf(gw[t], l, hl);
-    hh = fmaf(gw[t], h, hh);
+    const float2 v = lh[(2 * pi + t) * TO + pj];
+    ll = fmaf(hw[t], v.x, ll);
+    hi = fmaf(hw[t], v.y, hi);
+    hl = fmaf(gw[t], v.x, hl);
+    hh = fmaf(gw[t], v.y, hh);
   }
   auto put = [&](int c, float v) { sb[ko[c]] = A.clip ? clampf(old[c] + v, bnd[c]) : v; };
   if (A.level < A.levels) A.tmp[w * A.tmp_stride + A.out_off + size_t(qi) * mo + qj] = ll;
   else put(0, ll);
-  put(1, lh);
+  put(1, hi);
   put(2, hl);
   put(3, hh);
 }
@@ -149,8 +151,8 @@ __device__ __forceinline__ void analysis_tile(const DwtArgs& A, const float* __r
 __global__ __launch_bounds__(ST) void k_dwt_level(DwtArgs A, const float* __restrict__ filt,
                                                   const int* __restrict__ flen) {
   constexpr int RW = 2 * TO + MAX_TAPS - 2;
-  __shared__ float in[RW * RW];
-  __shared__ float lo[RW * TO], hi[RW * TO];
+  __shared__ __align__(8) float in[RW * RW];
+  __shared__ float2 lh[RW * TO];
   const int n = A.n;
   int tx, ty;
   band_tile(tx, ty);
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(ST) void k_dwt_level(DwtArgs A, const float* __rest
     }
     return;
   }
-#define RI_ANALYSIS(LL) analysis_tile<LL>(A, filt + z * FILT_STRIDE, z, i0, j0, in, lo, hi)
+#define RI_ANALYSIS(LL) analysis_tile<LL>(A, filt + z * FILT_STRIDE, z, i0, j0, in, lh)
   RI_SWITCH_L(flen[z], RI_ANALYSIS)
 #undef RI_ANALYSIS
 }
@@ -180,14 +182,14 @@ constexpr int RS = TS / 2 + MAX_TAPS / 2;  // LDS stride of a staged subband reg
 
 // Coefficients of one synthesis tile: output tile (p0, q0) of wavelet w (half filter
 // length H) reads rows / columns [p0 / 2 - H, p0 / 2 + TS / 2) and [q0 / 2 - H, ...) of
-// each of its four subbands (periodic).  A thread holds elements idx = threadIdx.x + e * ST
+// each of its four subbands (periodic).  Thread tid of 256 holds elements idx = tid + e * ST
 // of the RL x RL region, RL = TS / 2 + H, at (idx / RL, idx % RL).
 constexpr int STAGE_PER = (RS * RS + ST - 1) / ST;
 struct Stage {
   float v[4][STAGE_PER];
 };
 
-__device__ __forceinline__ void fetch_stage(const IdwtArgs& A, int w, int H, int p0, int q0, Stage& r) {
+__device__ __forceinline__ void fetch_stage(const IdwtArgs& A, int w, int H, int p0, int q0, int tid, Stage& r) {
   const int RL = TS / 2 + H;
   const int n = A.n, mo = A.m / 2, mk = A.m / 2 - 1;
   const int kr = p0 / 2 - H, kc = q0 / 2 - H;
@@ -197,7 +199,7 @@ __device__ __forceinline__ void fetch_stage(const IdwtArgs& A, int w, int H, int
   const int ll_stride = ll_coef ? n : mo;
 #pragma unroll
   for (int e = 0; e < STAGE_PER; ++e) {
-    const int idx = threadIdx.x + e * ST;
+    const int idx = tid + e * ST;
     if (idx >= RL * RL) break;
     const int ky = idx / RL, kx = idx - ky * RL;
     const int gy = (kr + ky) & mk, gx = (kc + kx) & mk;
@@ -208,58 +210,56 @@ __device__ __forceinline__ void fetch_stage(const IdwtArgs& A, int w, int H, int
   }
 }
 
-__device__ __forceinline__ void deposit_stage(int H, const Stage& r, float (*sb)[RS * RS]) {
+__device__ __forceinline__ void deposit_stage(int H, const Stage& r, int tid, float4* sb) {
   const int RL = TS / 2 + H;
 #pragma unroll
   for (int e = 0; e < STAGE_PER; ++e) {
-    const int idx = threadIdx.x + e * ST;
+    const int idx = tid + e * ST;
     if (idx >= RL * RL) break;
     const int ky = idx / RL, kx = idx - ky * RL;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) sb[c][ky * RS + kx] = r.v[c][e];
+    sb[ky * RS + kx] = make_float4(r.v[0][e], r.v[1][e], r.v[2][e], r.v[3][e]);
   }
 }
 
 // One synthesis level for one wavelet (filters of length L) on a tile whose coefficients
 // are staged in sb: out[2q + r] = sum_u h[2u + r] a[q - u] + g[2u + r] d[q - u] along each
-// axis (the transpose of the analysis), columns (y) first into lo / hi, then rows (x).
-// Returns through `emit(k, pl, q, v_even, v_odd)` the output pairs (p0 + pl, q0 + 2q +
-// {0, 1}).  Requires sb complete (a barrier after staging); ends after the barrier
-// between its two passes, so sb may be overwritten once it returns.
+// axis (the transpose of the analysis), columns (y) first into lh (low and high along x), then
+// rows (x).  Returns through `emit(k, pl, q, v_even, v_odd)` the output pairs (p0 + pl, q0 + 2q
+// + {0, 1}).  tid: the thread within the 256 that share sb and lh.  Requires sb complete (a
+// barrier after staging); ends after the barrier between its two passes, so sb may be
+// overwritten once it returns.  A coefficient's four subbands and a column sum's two halves lie
+// together in LDS, so that one instruction reads them.
 template <int L, class Emit>
-__device__ __forceinline__ void synthesis_staged(const float* __restrict__ hw, const float (*sb)[RS * RS],
-                                                 float* lo, float* hi, Emit& emit) {
+__device__ __forceinline__ void synthesis_staged(const float* __restrict__ hw, const float4* sb, float2* lh, int tid,
+                                                 Emit& emit) {
   const float* __restrict__ gw = hw + MAX_TAPS;
   constexpr int H = L / 2;
   constexpr int RL = TS / 2 + H;
-  for (int idx = threadIdx.x; idx < (TS / 2) * RL; idx += ST) {
+  for (int idx = tid; idx < (TS / 2) * RL; idx += ST) {
     const int qy = idx / RL, jl = idx - qy * RL;
-    float le = 0.f, lo_ = 0.f, he = 0.f, ho = 0.f;
+    float le = 0.f, lo = 0.f, he = 0.f, ho = 0.f;
 #pragma unroll
     for (int u = 0; u < H; ++u) {
-      const int k = (qy + H - u) * RS + jl;
-      const float a0 = sb[0][k], a1 = sb[1][k], a2 = sb[2][k], a3 = sb[3][k];
-      le = fmaf(hw[2 * u], a0, fmaf(gw[2 * u], a2, le));
-      lo_ = fmaf(hw[2 * u + 1], a0, fmaf(gw[2 * u + 1], a2, lo_));
-      he = fmaf(hw[2 * u], a1, fmaf(gw[2 * u], a3, he));
-      ho = fmaf(hw[2 * u + 1], a1, fmaf(gw[2 * u + 1], a3, ho));
+      const float4 c = sb[(qy + H - u) * RS + jl];
+      le = fmaf(hw[2 * u], c.x, fmaf(gw[2 * u], c.z, le));
+      lo = fmaf(hw[2 * u + 1], c.x, fmaf(gw[2 * u + 1], c.z, lo));
+      he = fmaf(hw[2 * u], c.y, fmaf(gw[2 * u], c.w, he));
+      ho = fmaf(hw[2 * u + 1], c.y, fmaf(gw[2 * u + 1], c.w, ho));
     }
-    lo[(2 * qy) * RS + jl] = le;
-    lo[(2 * qy + 1) * RS + jl] = lo_;
-    hi[(2 * qy) * RS + jl] = he;
-    hi[(2 * qy + 1) * RS + jl] = ho;
+    lh[(2 * qy) * RS + jl] = make_float2(le, he);
+    lh[(2 * qy + 1) * RS + jl] = make_float2(lo, ho);
   }
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < TS * TS / 2 / ST; ++k) {
-    const int idx = threadIdx.x + k * ST;
+    const int idx = tid + k * ST;
     const int pl = idx / (TS / 2), qx = idx - pl * (TS / 2);
     float ve = 0.f, vo = 0.f;
 #pragma unroll
     for (int u = 0; u < H; ++u) {
-      const float a = lo[pl * RS + qx + H - u], d = hi[pl * RS + qx + H - u];
-      ve = fmaf(hw[2 * u], a, fmaf(gw[2 * u], d, ve));
-      vo = fmaf(hw[2 * u + 1], a, fmaf(gw[2 * u + 1], d, vo));
+      const float2 c = lh[pl * RS + qx + H - u];
+      ve = fmaf(hw[2 * u], c.x, fmaf(gw[2 * u], c.y, ve));
+      vo = fmaf(hw[2 * u + 1], c.x, fmaf(gw[2 * u + 1], c.y, vo));
     }
     emit(k, pl, qx, ve, vo);
   }
@@ -267,8 +267,8 @@ __device__ __forceinline__ void synthesis_staged(const float* __restrict__ hw, c
 
 __global__ __launch_bounds__(ST) void k_idwt_level(IdwtArgs A, const float* __restrict__ filt,
                                                    const int* __restrict__ flen) {
-  __shared__ float sb[4][RS * RS];
-  __shared__ float lo[TS * RS], hi[TS * RS];
+  __shared__ float4 sb[RS * RS];
+  __shared__ float2 lh[TS * RS];
   const int w = blockIdx.z;
   int tx, ty;
   band_tile(tx, ty);
@@ -281,65 +281,102 @@ __global__ __launch_bounds__(ST) void k_idwt_level(IdwtArgs A, const float* __re
       out[size_t(p) * m + q + 1] = vo;
     }
   };
-  const int L = flen[w];
+  const int L = flen[w], tid = threadIdx.x;
   Stage r;
-  fetch_stage(A, w, L / 2, p0, q0, r);
-  deposit_stage(L / 2, r, sb);
+  fetch_stage(A, w, L / 2, p0, q0, tid, r);
+  deposit_stage(L / 2, r, tid, sb);
   __syncthreads();
-#define RI_SYNTH(LL) synthesis_staged<LL>(filt + w * FILT_STRIDE, sb, lo, hi, emit)
+#define RI_SYNTH(LL) synthesis_staged<LL>(filt + w * FILT_STRIDE, sb, lh, tid, emit)
   RI_SWITCH_L(L, RI_SYNTH)
 #undef RI_SYNTH
 }
 
-// Last level: each workgroup sums all wavelets' syntheses of its tile in registers.  The
-// coefficients of wavelet w + 1 are loaded into registers while wavelet w is computed and
-// moved to LDS after its column pass, so the loads overlap the arithmetic.
-__global__ __launch_bounds__(ST) void k_idwt_top(IdwtArgs A, const float* __restrict__ filt,
-                                                 const int* __restrict__ flen) {
+// Last level: each workgroup sums all wavelets' syntheses of its tile, in order.  Its TG groups
+// of 256 threads take the wavelets in turn (a long filter after a short one); a group loads its
+// next wavelet's coefficients into registers while the current one is computed.  With one group
+// the sums stay in registers; with four the wavelets' tiles are added through LDS, which
+// shortens the chain of eight loads, two passes and their barriers where there are too few
+// tiles to hide it, and costs where there are enough.  TOP_NUMBERS
+constexpr int TOP_GROUPS = 4;
+
+template <int TG>
+__global__ __launch_bounds__(ST * TG) void k_idwt_top(IdwtArgs A, const float* __restrict__ filt,
+                                                      const int* __restrict__ flen) {
   constexpr int PER = TS * TS / 2 / ST;  // output pairs per thread
-  __shared__ float sb[4][RS * RS];
-  __shared__ float lo[TS * RS], hi[TS * RS];
+  constexpr int ROUNDS = MAX_WAVELETS / TG;
+  __shared__ float4 sb[TG][RS * RS];
+  __shared__ float2 lh[TG][TS * RS];
+  const int grp = TG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / ST), tid = threadIdx.x % ST;
   int tx, ty;
   band_tile(tx, ty);
   const int p0 = ty * TS, q0 = tx * TS, n = A.n;
-  float acc_e[PER], acc_o[PER], dir[PER][2];
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    acc_e[k] = acc_o[k] = 0.f;
-    const int idx = threadIdx.x + k * ST;
-    const int p = p0 + idx / (TS / 2), q = q0 + 2 * (idx % (TS / 2));
-    const bool in = A.dirac && p < n && q < n;
-    dir[k][0] = in ? A.s[size_t(p) * n + q] : 0.f;
-    dir[k][1] = in ? A.s[size_t(p) * n + q + 1] : 0.f;
-  }
-  auto emit = [&](int k, int, int, float ve, float vo) {
-    acc_e[k] += ve;
-    acc_o[k] += vo;
+  auto wavelet = [&](int r) { return r * TG + (r % 2 == 0 ? grp : TG - 1 - grp); };
+  // the Dirac basis' pixels that this thread stores
+  constexpr int DIR = TG == 1 ? 2 * PER : 1;
+  static_assert(TG == 1 || TS * TS == ST * TG, "one output per thread");
+  auto pixel = [&](int k) {  // row << 16 | column, within the tile
+    if (TG > 1) return (int(threadIdx.x) / TS) << 16 | int(threadIdx.x) % TS;
+    const int idx = tid + (k / 2) * ST;
+    return (idx / (TS / 2)) << 16 | (2 * (idx % (TS / 2)) + k % 2);
   };
-  if (A.nw > 0) {
-    Stage r;
-    fetch_stage(A, 0, flen[0] / 2, p0, q0, r);
-    deposit_stage(flen[0] / 2, r, sb);
-    __syncthreads();
-    for (int w = 0; w < A.nw; ++w) {
-      const int L = flen[w];
-      const bool more = w + 1 < A.nw;
-      const int Hn = more ? flen[w + 1] / 2 : 0;
-      if (more) fetch_stage(A, w + 1, Hn, p0, q0, r);
-#define RI_SYNTH(LL) synthesis_staged<LL>(filt + w * FILT_STRIDE, sb, lo, hi, emit)
-      RI_SWITCH_L(L, RI_SYNTH)
+  float dir[DIR];
+#pragma unroll
+  for (int k = 0; k < DIR; ++k) {
+    const int p = p0 + (pixel(k) >> 16), q = q0 + (pixel(k) & 0xffff);
+    dir[k] = A.dirac && p < n && q < n ? A.s[size_t(p) * n + q] : 0.f;
+  }
+  float2 val[TG == 1 ? 1 : ROUNDS][PER];  // the sums, or each of the group's wavelets
+  if (TG == 1)
+#pragma unroll
+    for (int k = 0; k < PER; ++k) val[0][k] = make_float2(0.f, 0.f);
+  Stage st;
+  if (wavelet(0) < A.nw) {
+    fetch_stage(A, wavelet(0), flen[wavelet(0)] / 2, p0, q0, tid, st);
+    deposit_stage(flen[wavelet(0)] / 2, st, tid, sb[grp]);
+  }
+  __syncthreads();
+  auto round = [&](int r, float2* v) {
+    const int w = wavelet(r), wn = r + 1 < ROUNDS ? wavelet(r + 1) : A.nw;
+    const int Hn = wn < A.nw ? flen[wn] / 2 : 0;
+    if (wn < A.nw) fetch_stage(A, wn, Hn, p0, q0, tid, st);
+    if (w < A.nw) {
+      auto emit = [&](int k, int, int, float ve, float vo) {
+        v[k] = TG == 1 ? make_float2(v[k].x + ve, v[k].y + vo) : make_float2(ve, vo);
+      };
+#define RI_SYNTH(LL) synthesis_staged<LL>(filt + w * FILT_STRIDE, sb[grp], lh[grp], tid, emit)
+      RI_SWITCH_L(flen[w], RI_SYNTH)
 #undef RI_SYNTH
-      if (more) deposit_stage(Hn, r, sb);
+    } else {
       __syncthreads();
     }
+    if (wn < A.nw) deposit_stage(Hn, st, tid, sb[grp]);
+    __syncthreads();
+  };
+  if constexpr (TG == 1) {
+    for (int r = 0; r < A.nw; ++r) round(r, val[0]);
+  } else {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) round(r, val[r]);
+  }
+  float* part = reinterpret_cast<float*>(&sb[0][0]);  // [wavelet][row][column]
+  if (TG > 1) {
+    static_assert(TG == 1 || sizeof(float) * MAX_WAVELETS * TS * TS <= sizeof(sb), "the tiles take the place of sb");
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+      if (wavelet(r) < A.nw)
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+          reinterpret_cast<float2*>(part + wavelet(r) * TS * TS)[tid + k * ST] = val[TG == 1 ? 0 : r][k];
+    __syncthreads();
   }
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int idx = threadIdx.x + k * ST;
-    const int p = p0 + idx / (TS / 2), q = q0 + 2 * (idx % (TS / 2));
-    if (p >= n || q >= n) continue;
-    A.x[size_t(p) * n + q] = acc_e[k] + dir[k][0];
-    A.x[size_t(p) * n + q + 1] = acc_o[k] + dir[k][1];
+  for (int k = 0; k < DIR; ++k) {
+    const int p = p0 + (pixel(k) >> 16), q = q0 + (pixel(k) & 0xffff);
+    float acc = 0.f;
+    if (TG == 1) acc = k % 2 == 0 ? val[0][k / 2].x : val[0][k / 2].y;
+    else
+      for (int w = 0; w < A.nw; ++w) acc += part[w * TS * TS + threadIdx.x];
+    if (p < n && q < n) A.x[size_t(p) * n + q] = acc + dir[k];
   }
 }
 
@@ -375,7 +412,10 @@ int synthesis_lower(const Sara& S, const float* s, hipStream_t st) {
 int synthesis_top(const Sara& S, const float* s, float* x, hipStream_t st) {
   IdwtArgs A{s, S.tmp, S.tmp_stride, S.levels > 1 ? S.tmp_off[1] : 0, 0, S.n, S.n, 1, S.levels, S.dirac, S.nw, x};
   const dim3 g(tiles(S.n, TS), tiles(S.n, TS));
-  hipLaunchKernelGGL(k_idwt_top, g, dim3(ST), 0, st, A, S.dfilt, S.dlen);
+  if (g.x * g.y <= 2 * 256)  // at most two tiles per CU
+    hipLaunchKernelGGL(k_idwt_top<TOP_GROUPS>, g, dim3(ST * TOP_GROUPS), 0, st, A, S.dfilt, S.dlen);
+  else
+    hipLaunchKernelGGL(k_idwt_top<1>, g, dim3(ST), 0, st, A, S.dfilt, S.dlen);
   RI_LAUNCH_CHECK();
   return RI_OK;
 }
