@@ -11,6 +11,7 @@
 // the real part, scaled by S.
 #include "fft.hpp"
 #include "plan.hpp"
+#include "sara_dev.hpp"
 
 namespace ri {
 
@@ -32,11 +33,15 @@ struct ColCfg {
   static constexpr int NT = K <= 512 ? 256 : 512;
 };
 
-// Adjoint column panels of windowed plans: a wavefront or more per four columns.
+// Adjoint column panels of windowed plans.  Up to SIDE_K a sparsity job may ride on the launch
+// (KIND), whose workgroup size decides the panel; launches without a job use the same kernel, so
+// that both give the same bits (another instance may contract its products differently).
 template <int K>
 struct WinColCfg {
-  static constexpr int W = 4;
-  static constexpr int NT = W * K / 16 < 64 ? 64 : W * K / 16;
+  static constexpr int KIND = K < SIDE_K ? SIDE_TOP : (K == SIDE_K ? SIDE_IDWT : SIDE_NONE);
+  static constexpr int W = K <= SIDE_K ? 8 : 4;
+  static constexpr int NT = KIND == SIDE_TOP ? ST * TOP_GROUPS : 256;
+  static constexpr int RADIX = K >= 256 ? 16 : 8;
 };
 
 // Column panel of workgroup b of nb: consecutive blocks go round-robin to the eight XCDs,
@@ -113,13 +118,22 @@ __global__ __launch_bounds__(NT) void k_adj_cols(const float2* __restrict__ grid
 constexpr int REACH = KB_J - 1;
 constexpr int SHIFT = KB_J / 2 - 1;
 
-template <int K, int W, int NT>
+// KIND: the workgroups after the K / W panels' are those of a sparsity job.
+template <int K, int W, int NT, int KIND>
 __global__ __launch_bounds__(NT) void k_adj_cols_win(const float2* __restrict__ patch, float2* __restrict__ rows,
-                                                     const float2* __restrict__ tw) {
+                                                     const float2* __restrict__ tw, SideJob side) {
   constexpr int n = K / 2, TA = K / GSIDE;
-  __shared__ float2 lds[K * W];
-  __shared__ float2 twl[TwLds<K, W>::size];
-  const int c0 = panel_of(blockIdx.x, gridDim.x) * W;
+  constexpr int OWN = (K * W + TwLds<K, W>::size) * int(sizeof(float2)), JOB = KIND != SIDE_NONE ? side_smem<NT>() : 0;
+  __shared__ __align__(16) char smem[OWN > JOB ? OWN : JOB];
+  if constexpr (KIND != SIDE_NONE) {
+    if (blockIdx.x >= K / W) {
+      side_body<NT, KIND>(side, int(blockIdx.x) - K / W, smem);
+      return;
+    }
+  }
+  float2* lds = reinterpret_cast<float2*>(smem);
+  float2* twl = lds + K * W;
+  const int c0 = panel_of(blockIdx.x, K / W) * W;
   // the data branch's kernels issue ahead of the sparsity branch's waves sharing their SIMDs
   __builtin_amdgcn_s_setprio(3);
   auto load = [&](int w, int k) -> float2 {
@@ -138,7 +152,7 @@ __global__ __launch_bounds__(NT) void k_adj_cols_win(const float2* __restrict__ 
     const int r = pix_of(q, n, K);
     if (r >= 0) rows[size_t(r) * K + ((c0 + w - SHIFT) & (K - 1))] = v;
   };
-  FftPanel<K, W, NT, +1, true>::template run<TwLds<K, W>::fits>(lds, tw, twl, load, store);
+  FftPanel<K, W, NT, +1, true, WinColCfg<K>::RADIX>::template run<TwLds<K, W>::fits>(lds, tw, twl, load, store);
 }
 
 // UPD: the output g = Re S (...) feeds steps 17-18 (PrimalUpdate) instead of being stored.
@@ -181,7 +195,10 @@ __global__ __launch_bounds__(NT) void k_adj_rows(const float2* __restrict__ rows
           xo = u.x[o];
           so = u.st[o];
         }
-        const float xn = fmaxf(0.f, xo - u.tau * (u.sigma * so + u.varsigma * g));
+        float gr;
+        if constexpr (K <= WINDOWED_K) gr = fmaf(u.varsigma, g, fmaf(u.varsigma_lo, g, u.sigma * so));
+        else gr = u.sigma * so + u.varsigma * g;
+        const float xn = fmaxf(0.f, xo - u.tau * gr);
         u.x[o] = xn;
         u.xt[o] = 2.f * xn - xo;
       } else {
@@ -211,11 +228,13 @@ int fwd_cols_impl(const Plan& p, const float*, float2* grid, hipStream_t s) {
 }
 
 template <int K>
-int adj_cols_impl(const Plan& p, const float2* grid, float*, hipStream_t s) {
+int adj_cols_impl(const Plan& p, const float2* grid, const SideJob* side, hipStream_t s) {
+  const int jobs = side != nullptr ? side->wgs : 0;
+  if (jobs > 0 && K > SIDE_K) return fail(RI_EINVAL, "adjoint column pass: no side job at K=%d", K);
   if constexpr (K <= WINDOWED_K) {
     using WC = WinColCfg<K>;
-    hipLaunchKernelGGL((k_adj_cols_win<K, WC::W, WC::NT>), dim3(K / WC::W), dim3(WC::NT), 0, s, grid, p.rowbuf,
-                       p.twiddle);
+    hipLaunchKernelGGL((k_adj_cols_win<K, WC::W, WC::NT, WC::KIND>), dim3(K / WC::W + jobs), dim3(WC::NT), 0, s, grid,
+                       p.rowbuf, p.twiddle, jobs > 0 ? *side : SideJob{});
   } else {
     using CC = ColCfg<K>;
     hipLaunchKernelGGL((k_adj_cols<K, CC::W, CC::NT>), dim3(K / CC::W), dim3(CC::NT), 0, s, grid, p.rowbuf,
@@ -266,8 +285,8 @@ int fft_forward_cols(const Plan& p, float2* grid, hipStream_t s) {
   RI_FFT_DISPATCH(fwd_cols_impl, p, nullptr, grid, s)
 }
 
-int fft_adjoint_cols(const Plan& p, const float2* grid, hipStream_t s) {
-  RI_FFT_DISPATCH(adj_cols_impl, p, grid, nullptr, s)
+int fft_adjoint_cols(const Plan& p, const float2* grid, hipStream_t s, const SideJob* side) {
+  RI_FFT_DISPATCH(adj_cols_impl, p, grid, side, s)
 }
 
 int fft_adjoint_rows(const Plan& p, float* x, hipStream_t s) {

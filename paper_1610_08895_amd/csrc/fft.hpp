@@ -114,10 +114,11 @@ __device__ __forceinline__ void dft(float2* a) {
   else dft16<DIR>(a);
 }
 
-template <int K, int W, int NT, int DIR, bool WFAST>
+// RADIX: of the passes after the first (0: by the rule above).
+template <int K, int W, int NT, int DIR, bool WFAST, int RADIX = 0>
 struct FftPanel {
   static constexpr int LOGK = clog2(K);
-  static constexpr int RB = W * (K / 16) >= NT ? 16 : 8;  // radix of the passes after the first
+  static constexpr int RB = RADIX != 0 ? RADIX : (W * (K / 16) >= NT ? 16 : 8);
   static constexpr int LB = clog2(RB);
   static constexpr int R0 = LOGK % LB == 0 ? RB : (1 << (LOGK % LB));
   static constexpr int NPASS = LOGK % LB == 0 ? LOGK / LB : LOGK / LB + 1;

@@ -38,6 +38,7 @@
 // wavefront evenly over the LDS banks of the staged tile.  Items whose values are all zero
 // (a block whose dual did not change) are skipped.
 #include "plan.hpp"
+#include "sara_dev.hpp"
 
 namespace ri {
 
@@ -83,7 +84,8 @@ static_assert((Pitch<32>::TW - 32) * Pitch<32>::TW + 32 * (Pitch<32>::TW - 32) =
 // MAX_BIN / GT) visibilities of an item before computing any, and the residual norms of
 // an item are left as one FP64 partial pair per wavefront (part[(item * NWAVES + w) * 2],
 // item = its index in block order).
-template <int T, int MODE>
+// SIDE: workgroups from ustride on are those of a sparsity job instead.
+template <int T, int MODE, bool SIDE>
 __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, int nunits,
                                                const Item* __restrict__ items,
                                                const uint32_t* __restrict__ item_pairs,
@@ -92,14 +94,22 @@ __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, i
                                                int tpa, KBPoly P, float2* __restrict__ out,
                                                const float2* __restrict__ y, const float2* __restrict__ v,
                                                double* __restrict__ part, int ustride,
-                                               float2* __restrict__ zero_grid, const int* __restrict__ zero_tiles) {
+                                               float2* __restrict__ zero_grid, const int* __restrict__ zero_tiles, SideJob side) {
   constexpr int TW = Pitch<T>::TW, TP = Pitch<T>::TP;
   constexpr int NV = MAX_BIN / GT;
   constexpr int NWV = GT / 64;
   static_assert(GT == GRID_LANES && NV == 4, "the item order's slot pairs (item_order)");
+  constexpr int TILE_BYTES = TW * TP * int(sizeof(float2));
+  __shared__ __align__(16) char smem[SIDE && side_smem<GT>() > TILE_BYTES ? side_smem<GT>() : TILE_BYTES];
+  if constexpr (SIDE) {
+    if (int(blockIdx.x) >= ustride) {
+      side_body<GT, SIDE_DWT>(side, int(blockIdx.x) - ustride, smem);
+      return;
+    }
+  }
   // the data branch's kernels issue ahead of the sparsity branch's waves sharing their SIMDs
   __builtin_amdgcn_s_setprio(3);
-  __shared__ float2 tile[TW * TP];
+  float2* tile = reinterpret_cast<float2*>(smem);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (int(blockIdx.x) >= ustride) {
     // a further workgroup: zeroes the interior of one tile without visibilities in
@@ -229,13 +239,22 @@ __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, i
 }
 
 // stats[2i], stats[2i+1] = sums of the per-item, per-wavefront partials of block i, for
-// active blocks; a copy goes to out (if not null), with NaN for inactive blocks.
+// active blocks; a copy goes to out (if not null), with NaN for inactive blocks.  SIDE: the
+// workgroups after the d blocks' are those of a sparsity job.
+template <bool SIDE>
 __global__ __launch_bounds__(GT) void k_block_stats(const uint8_t* __restrict__ mask, const int* __restrict__ item_off,
                                                     const double* __restrict__ part, double* __restrict__ stats,
                                                     double* __restrict__ out, const double* __restrict__ eps,
-                                                    float* __restrict__ shrink) {
+                                                    float* __restrict__ shrink, int d, SideJob side) {
   __shared__ double red[2][GT / 64];
   const int i = blockIdx.x;
+  if constexpr (SIDE) {
+    __shared__ __align__(16) char smem[side_smem<GT>()];
+    if (i >= d) {
+      side_body<GT, SIDE_DWT>(side, i - d, smem);
+      return;
+    }
+  }
   // the data branch's kernels issue ahead of the sparsity branch's waves sharing their SIMDs
   __builtin_amdgcn_s_setprio(3);
   if (mask != nullptr && mask[i] == 0) {
@@ -804,10 +823,14 @@ int block_sumsq(const Plan& p, const float2* y, double* out, hipStream_t s) {
 }
 
 int block_stats(const Plan& p, const uint8_t* mask, double* stats, double* out, hipStream_t s, const double* eps,
-                float* shrink, const double* part) {
+                float* shrink, const double* part, const SideJob* side) {
   if ((eps == nullptr) != (shrink == nullptr)) return fail(RI_EINVAL, "block_stats: eps and shrink go together");
-  hipLaunchKernelGGL(k_block_stats, dim3(p.d), dim3(GT), 0, s, mask, p.item_off, part ? part : p.item_part, stats,
-                     out, eps, shrink);
+  if (side != nullptr && side->wgs > 0)
+    hipLaunchKernelGGL(k_block_stats<true>, dim3(p.d + side->wgs), dim3(GT), 0, s, mask, p.item_off,
+                       part ? part : p.item_part, stats, out, eps, shrink, p.d, *side);
+  else
+    hipLaunchKernelGGL(k_block_stats<false>, dim3(p.d), dim3(GT), 0, s, mask, p.item_off,
+                       part ? part : p.item_part, stats, out, eps, shrink, p.d, SideJob{});
   RI_LAUNCH_CHECK();
   return RI_OK;
 }
@@ -819,12 +842,21 @@ namespace {
 // zero (or null).
 template <int T, int MODE>
 int degrid_batched_t(const Plan& p, const float2* grid, float2* out, const float2* y, const float2* v,
-                     double* part, const uint8_t* mask, float2* zero, hipStream_t s) {
+                     double* part, const uint8_t* mask, float2* zero, hipStream_t s, const SideJob* side) {
   const int g = wgs_for(p, p.n_dunits), extra = zero != nullptr ? p.n_empty : 0;
+  if constexpr (MODE == DG_RESIDUAL) {
+    if (side != nullptr && side->wgs > 0) {
+      hipLaunchKernelGGL((k_degrid<T, MODE, true>), dim3(g + side->wgs), dim3(GT), 0, s, p.dunits, p.n_dunits,
+                         p.titems, p.item_pairs, mask, p.coord, grid, p.K, p.tpa, p.poly, out, y, v, part, g,
+                         (float2*)nullptr, (const int*)nullptr, *side);
+      RI_LAUNCH_CHECK();
+      return RI_OK;
+    }
+  }
   if (p.n_dunits > 0 || extra > 0) {
-    hipLaunchKernelGGL((k_degrid<T, MODE>), dim3(g + extra), dim3(GT), 0, s, p.dunits, p.n_dunits, p.titems,
+    hipLaunchKernelGGL((k_degrid<T, MODE, false>), dim3(g + extra), dim3(GT), 0, s, p.dunits, p.n_dunits, p.titems,
                        p.item_pairs, mask, p.coord, grid, p.K, p.tpa, p.poly, out, y, v, part, g, zero,
-                       p.empty_tiles);
+                       p.empty_tiles, SideJob{});
     RI_LAUNCH_CHECK();
   }
   return RI_OK;
@@ -832,11 +864,11 @@ int degrid_batched_t(const Plan& p, const float2* grid, float2* out, const float
 
 template <int MODE>
 int degrid_batched(const Plan& p, const float2* grid, float2* out, const float2* y, const float2* v, double* part,
-                   const uint8_t* mask, hipStream_t s, float2* zero = nullptr) {
+                   const uint8_t* mask, hipStream_t s, float2* zero = nullptr, const SideJob* side = nullptr) {
   switch (p.tile) {
-    case 16: return degrid_batched_t<16, MODE>(p, grid, out, y, v, part, mask, zero, s);
-    case 32: return degrid_batched_t<32, MODE>(p, grid, out, y, v, part, mask, zero, s);
-    case 64: return degrid_batched_t<64, MODE>(p, grid, out, y, v, part, mask, zero, s);
+    case 16: return degrid_batched_t<16, MODE>(p, grid, out, y, v, part, mask, zero, s, side);
+    case 32: return degrid_batched_t<32, MODE>(p, grid, out, y, v, part, mask, zero, s, side);
+    case 64: return degrid_batched_t<64, MODE>(p, grid, out, y, v, part, mask, zero, s, side);
     default: return fail(RI_EINVAL, "unsupported tile %d", p.tile);
   }
 }
@@ -849,12 +881,14 @@ int degrid_apply(const Plan& p, const float2* grid, float2* y, const uint8_t* ma
 }
 
 int degrid_residual(const Plan& p, const float2* grid, const float2* y, const float2* v, float2* e,
-                    const uint8_t* mask, hipStream_t s, float2* zero_empty) {
+                    const uint8_t* mask, hipStream_t s, float2* zero_empty, const SideJob* side) {
+  if (side != nullptr && side->wgs > 0 && (p.dde.on() || !p.windowed || zero_empty != nullptr))
+    return fail(RI_EINVAL, "degrid_residual: no side job here");
   if (p.dde.on()) {
     if (zero_empty != nullptr) return fail(RI_EINVAL, "degrid_residual: no tile zeroing with DDEs");
     return dde_degrid(p, p.dunits, p.n_dunits, p.titems, mask, grid, e, y, v, p.item_part, s);
   }
-  return degrid_batched<DG_RESIDUAL>(p, grid, e, y, v, p.item_part, mask, s, zero_empty);
+  return degrid_batched<DG_RESIDUAL>(p, grid, e, y, v, p.item_part, mask, s, zero_empty, side);
 }
 
 int degrid_norms(const Plan& p, const float2* grid, const float2* y, const float2* v, double* part, hipStream_t s) {
@@ -868,8 +902,8 @@ int degrid_residual_block(const Plan& p, int block, const float2* grid, const fl
   if (p.dde.on()) return dde_degrid(p, p.bunits + a, b - a, p.items, nullptr, grid, e, y, v, p.item_part, s);
   const dim3 grid_dim(wgs_for(p, b - a));
 #define ARGS p.bunits + a, b - a, p.items, p.item_pairs, (const uint8_t*)nullptr, p.coord, grid, p.K, p.tpa, \
-             p.poly, e, y, v, p.item_part, int(grid_dim.x), (float2*)nullptr, (const int*)nullptr
-  RI_TILE_DISPATCH(k_degrid, DG_RESIDUAL)
+             p.poly, e, y, v, p.item_part, int(grid_dim.x), (float2*)nullptr, (const int*)nullptr, SideJob{}
+  RI_TILE_DISPATCH(k_degrid, DG_RESIDUAL, false)
 #undef ARGS
   RI_LAUNCH_CHECK();
   return RI_OK;

@@ -147,8 +147,14 @@ int refresh_sum(ri_pd_s* P, hipStream_t s) {
   return grid_all(p, P->v, P->sum, s);
 }
 
+PrimalUpdate primal_update(ri_pd_s* P) {
+  const float vs = float(P->prm.varsigma);
+  return PrimalUpdate{P->st, P->x, P->xt, float(P->prm.tau), float(P->prm.sigma), vs, float(P->prm.varsigma - vs)};
+}
+
 int sparsity_branch(ri_pd_s* P, hipStream_t s) {
   // step 13 (Moreau form of the soft-threshold), then step 14
+  if (!P->timing || capturing(s)) return sparsity_apply(*P->sara, P->xt, P->s, P->alpha, P->wts, P->st, s);
   RI_STAGE(P, RI_STAGE_PSI_ADJ, s, psi_adj_apply(*P->sara, P->xt, P->s, true, P->alpha, s, P->wts));
   RI_STAGE(P, RI_STAGE_PSI_SYNTH, s, psi_apply(*P->sara, P->s, P->st, s));
   return RI_OK;
@@ -266,7 +272,33 @@ int ri_pd_step(ri_pd P, const uint8_t* mask, double* stats, hipStream_t stream) 
   // data branch is enqueued (and, under capture, recorded) before the sparsity branch: a
   // replayed graph then keeps it on the queue of the forward FFT, so neither the fork nor
   // the join (the sparsity branch ends first) puts a wait between two queues on its path.
-  const bool fork = !(P->timing && !ri::capturing(stream));
+  const bool timed = P->timing && !ri::capturing(stream);
+  ri::SideJobs job;
+  if (!timed && p.windowed && p.K <= ri::SIDE_K && !p.dde.on() &&
+      ri::side_jobs(*P->sara, P->xt, P->s, P->alpha, P->wts, P->st, job)) {
+    // Small problems: the sparsity branch rides on the data branch's launches as further
+    // workgroups.  A kernel there takes 3 to 9 us whatever it does, so the number of launches
+    // decides the time, and a second queue adds waits between the two: an iteration at 64^2
+    // 66 -> 42 us, at 256^2 89 -> 82; at 512^2, where kernels take 10 to 30 us, the second queue
+    // is the better one (109 us against 134 with every launch on one queue).
+    RI_TRY(ri::degrid_residual(p, p.grid, P->y, P->v, P->e, mask, stream, nullptr, &job.first));
+    RI_TRY(ri::block_stats(p, mask, P->stats, stats, stream, P->eps, P->shrink, nullptr, &job.second));
+    if (mask == nullptr)
+      RI_TRY(ri::win_project_all(p, P->e, P->v, P->shrink, P->sum, stream, &job.deep));
+    else
+      RI_TRY(ri::win_project(p, P->e, P->v, P->shrink, mask, P->sum, stream, &job.deep));
+    if (p.K == ri::SIDE_K) {
+      RI_TRY(ri::fft_adjoint_cols(p, P->sum, stream, &job.lower));
+      RI_TRY(ri::side_top(*P->sara, job.top, stream));
+    } else {
+      RI_TRY(ri::fft_adjoint_cols(p, P->sum, stream, &job.top));
+    }
+    const ri::PrimalUpdate upd = ri::primal_update(P);
+    RI_TRY(ri::fft_adjoint_rows_update(p, upd, stream));
+    P->iter += 1;
+    return RI_OK;
+  }
+  const bool fork = !timed;
   if (fork) RI_HIP(hipEventRecord(P->ev_fork, stream));
   // every block active (no mask): the sum is rebuilt from the new duals, reading r only
   // (the degridding launch also zeroes its tiles without visibilities); otherwise the active
@@ -290,7 +322,7 @@ int ri_pd_step(ri_pd P, const uint8_t* mask, double* stats, hipStream_t stream) 
   } else {
     RI_TRY(ri::sparsity_branch(P, stream));
   }
-  const ri::PrimalUpdate upd{P->st, P->x, P->xt, float(P->prm.tau), float(P->prm.sigma), float(P->prm.varsigma)};
+  const ri::PrimalUpdate upd = ri::primal_update(P);
   RI_STAGE(P, RI_STAGE_IFFT_ROWS, stream, ri::fft_adjoint_rows_update(p, upd, stream));
   P->iter += 1;
   return RI_OK;
@@ -340,7 +372,7 @@ int ri_pd_step_plain(ri_pd P, const uint8_t* mask_host, double* stats, hipStream
   RI_STAGE(P, RI_STAGE_GRID_HALO, stream, ri::grid_blocks_end(p, P->sum, stream));
   RI_STAGE(P, RI_STAGE_IFFT_COLS, stream, ri::fft_adjoint_cols(p, P->sum, stream));
   if (fork) RI_HIP(hipStreamWaitEvent(stream, P->ev_join, 0));
-  const ri::PrimalUpdate upd{P->st, P->x, P->xt, float(P->prm.tau), float(P->prm.sigma), float(P->prm.varsigma)};
+  const ri::PrimalUpdate upd = ri::primal_update(P);
   RI_STAGE(P, RI_STAGE_IFFT_ROWS, stream, ri::fft_adjoint_rows_update(p, upd, stream));
   P->iter += 1;
   return RI_OK;

@@ -165,6 +165,30 @@ uint32_t item_order(KV* kv, int64_t w, int T) {
   return uint32_t(p0) | uint32_t(p1) << 16;
 }
 
+// Fourier transform at f of the kernel that the tap polynomials make up: tap j at distance
+// t = g + 3 - j, g in [0, 1), weighs E_j(x^2) + x O_j(x^2), x = 2 g - 1, and tap 7 - j the
+// mirrored value, so the pair contributes 2 w cos(2 pi f t).  Gauss-Legendre on 12 nodes:
+// exact for degree 23, the integrand's degree 7 times a cosine of less than pi / 2 per unit.
+double poly_hat(const KBPoly& P, double f) {
+  static const double node[6] = {0.1252334085114689, 0.3678314989981802, 0.5873179542866175,
+                                 0.7699026741943047, 0.9041172563704749, 0.9815606342467193};
+  static const double weight[6] = {0.2491470458134028, 0.2334925365383548, 0.2031674267230659,
+                                   0.1600783285433462, 0.1069393259953184, 0.0471753363865118};
+  double sum = 0.0;
+  for (int j = 0; j < KB_J / 2; ++j)
+    for (int k = 0; k < 12; ++k) {
+      const double x = k < 6 ? node[k] : -node[k - 6], x2 = x * x;
+      double e = P.e[j][KB_HALF_DEG], o = P.o[j][KB_HALF_DEG];
+      for (int q = KB_HALF_DEG - 1; q >= 0; --q) {
+        e = e * x2 + P.e[j][q];
+        o = o * x2 + P.o[j][q];
+      }
+      const double t = 0.5 * (x + 1.0) + (KB_J / 2 - 1) - j;
+      sum += weight[k % 6] * 0.5 * 2.0 * (e + x * o) * std::cos(2.0 * M_PI * f * t);
+    }
+  return sum;
+}
+
 int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t* off, int J, double beta,
                 const ri_tuning* tune, hipStream_t s) {
   if (!is_pow2(n) || n < 16 || n > 2048) return fail(RI_EINVAL, "n=%d must be a power of two in [16, 2048]", n);
@@ -497,7 +521,13 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
     tw[k] = make_float2(float(std::cos(a)), float(std::sin(a)));
   }
   std::vector<float> sc(n);
-  for (int r = 0; r < n; ++r) sc[r] = float(1.0 / kb_hat(double(r - n / 2) / K, J, p.beta));
+  // Windowed plans take the transform of the kernel that is evaluated, its FP32 coefficients
+  // included: their rounding alone (3e-8 of the weights, the same for every visibility) would
+  // scale Phi, and through many iterations decide the error of gradients.
+  for (int r = 0; r < n; ++r) {
+    const double f = double(r - n / 2) / K;
+    sc[r] = float(1.0 / (p.windowed ? poly_hat(p.poly, f) : kb_hat(f, J, p.beta)));
+  }
 
   RI_TRY(dev_alloc(&p.coord, M));
   RI_TRY(upload(&p.order, p.order_host, s));

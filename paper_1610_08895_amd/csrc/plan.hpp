@@ -43,6 +43,8 @@ __device__ __forceinline__ void kb_weights(unsigned packed, const KBPoly& P, flo
   }
 }
 
+struct SideJob;  // sara.hpp
+
 // A work item: up to `bin` visibilities of one block that fall in one grid tile.
 // x = block, y = tile (ty * tiles_per_axis + tx), z = first plan position, w = count.
 // The device copies carry in y the item's index in block order instead (which indexes the
@@ -64,6 +66,7 @@ constexpr int DUNIT_VIS_MIN = 256;
 // slot of PATCH_W x PATCH_W (the last row and column stay zero).  The grid of the adjoint
 // exists as these patches only: a cell's value is the sum over the regions that cover it.
 constexpr int WINDOWED_K = 1024;
+constexpr int SIDE_K = 512;  // largest grid whose step runs both branches in the same launches
 constexpr int WIN = 8;
 constexpr int GSIDE = 16;
 constexpr int PATCH_W = 24;
@@ -172,7 +175,9 @@ int fft_adjoint(const Plan& p, const float2* grid, float* x, hipStream_t s);
 // The two passes of each, through the plan's n x K row buffer.
 int fft_forward_rows(const Plan& p, const float* x, hipStream_t s);
 int fft_forward_cols(const Plan& p, float2* grid, hipStream_t s);
-int fft_adjoint_cols(const Plan& p, const float2* grid, hipStream_t s);
+// side (grids of up to SIDE_K cells per axis only): a job added to the launch, SIDE_IDWT at
+// SIDE_K and SIDE_TOP below it.
+int fft_adjoint_cols(const Plan& p, const float2* grid, hipStream_t s, const SideJob* side = nullptr);
 int fft_adjoint_rows(const Plan& p, float* x, hipStream_t s);
 // Steps 17-18 fused into the adjoint row pass: with g = Re S Z^dagger F^dagger of the
 // plan's row buffer, x <- max(0, x - tau (sigma st + varsigma g)) and xt = 2 x_new - x_old,
@@ -182,6 +187,7 @@ struct PrimalUpdate {
   float* x;
   float* xt;
   float tau, sigma, varsigma;
+  float varsigma_lo;  // what varsigma lost in rounding (added on grids of up to WINDOWED_K)
 };
 int fft_adjoint_rows_update(const Plan& p, const PrimalUpdate& u, hipStream_t s);
 
@@ -189,9 +195,10 @@ int fft_adjoint_rows_update(const Plan& p, const PrimalUpdate& u, hipStream_t s)
 // stats[2i], stats[2i+1] = per-block sums of the degridding partials, active blocks only;
 // copied to out (may be null) with NaN rows for inactive blocks.  With eps and shrink
 // given, also shrink[i] = max(0, 1 - eps_i / ||r_i||) (0 inside the ball) for active blocks.
-// part: the per-item partials to reduce (null: the plan's).
+// part: the per-item partials to reduce (null: the plan's).  side: a SIDE_DWT job (or null).
 int block_stats(const Plan& p, const uint8_t* mask, double* stats, double* out, hipStream_t s,
-                const double* eps = nullptr, float* shrink = nullptr, const double* part = nullptr);
+                const double* eps = nullptr, float* shrink = nullptr, const double* part = nullptr,
+                const SideJob* side = nullptr);
 // out[i] = ||y_i||^2 (FP64) for every block.
 int block_sumsq(const Plan& p, const float2* y, double* out, hipStream_t s);
 // y = G b for the items of active blocks (operator form).
@@ -203,9 +210,10 @@ int grid_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* grid
 // ||G_i b_i - y_i||^2 for the blocks whose items are processed (per-item partial sums, then
 // a per-block reduction).  All items (those of inactive blocks skipped), or one block's.
 // zero_empty (not with DDEs): a grid whose tiles without visibilities the same launch sets
-// to zero (for grid_project_all(..., zeroed = true), which then skips that).
+// to zero (for grid_project_all(..., zeroed = true), which then skips that).  side (windowed
+// plans without DDEs): a SIDE_DWT job.
 int degrid_residual(const Plan& p, const float2* grid, const float2* y, const float2* v, float2* e,
-                    const uint8_t* mask, hipStream_t s, float2* zero_empty = nullptr);
+                    const uint8_t* mask, hipStream_t s, float2* zero_empty = nullptr, const SideJob* side = nullptr);
 // The norms of degrid_residual over all items, without storing e, into the given partials
 // (2 * PART_WAVES * n_items doubles).
 int degrid_norms(const Plan& p, const float2* grid, const float2* y, const float2* v, double* part, hipStream_t s);
@@ -237,9 +245,11 @@ int grid_all(const Plan& p, const float2* v, float2* grid, hipStream_t s);
 
 // ---- window.hip: the gridding of windowed plans ----
 int win_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* patch, hipStream_t s);
+// side (grids of up to SIDE_K cells per axis): a SIDE_DEEP job
 int win_project(const Plan& p, const float2* e, float2* v, const float* shrink, const uint8_t* mask, float2* patch,
-                hipStream_t s);
-int win_project_all(const Plan& p, const float2* r, float2* v, const float* shrink, float2* patch, hipStream_t s);
+                hipStream_t s, const SideJob* side = nullptr);
+int win_project_all(const Plan& p, const float2* r, float2* v, const float* shrink, float2* patch, hipStream_t s,
+                    const SideJob* side = nullptr);
 int win_project_block(const Plan& p, int block, const float2* e, float2* v, const float* shrink, float2* patch,
                       hipStream_t s);
 

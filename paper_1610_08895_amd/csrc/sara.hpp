@@ -40,6 +40,60 @@ int psi_adj_apply(const Sara& S, const float* x, float* s, bool clip, float alph
                   const float* wts = nullptr);
 // x = Psi s.
 int psi_apply(const Sara& S, const float* s, float* x, hipStream_t st);
+// Steps 13 and 14: the clipped analysis of x into s, then out = Psi s (bit for bit the two calls
+// above, in fewer launches where levels are small).
+int sparsity_apply(const Sara& S, const float* x, float* s, float alpha, const float* wts, float* out, hipStream_t st);
 
+// ---- kernel arguments ----
+struct DwtArgs {
+  const float* x;  // level-1 input (n x n)
+  float* tmp;
+  size_t tmp_stride, in_off, out_off;
+  float* s;
+  int n, m, level, levels, dirac, nw;
+  int clip;
+  float alpha;
+  const float* wts;  // per-coefficient weights of the clip bound (layout of s), or null
+};
+
+
+struct IdwtArgs {
+  const float* s;
+  float* tmp;
+  size_t tmp_stride, ll_off, out_off;
+  int n, m, level, levels, dirac, nw;
+  float* x;  // top level only: the image Psi s
+};
+
+constexpr int DEEP = 64;  // largest input of the deep levels
+struct DeepArgs {
+  DwtArgs a;
+  int first;      // first level
+  size_t ll_off;  // offset of its input (analysis) and output (synthesis) in a wavelet's scratch
+  int analyse, synth;
+};
+
+// The sparsity branch cut into jobs that ride on the launches of the data branch, as workgroups
+// added to theirs (wgs = 0: nothing to add).
+enum { SIDE_NONE = 0, SIDE_DWT = 1, SIDE_IDWT = 2, SIDE_DEEP = 3, SIDE_TOP = 4 };
+struct SideJob {
+  int wgs = 0, nx = 0, ny = 0;
+  const float* filt = nullptr;
+  const int* flen = nullptr;
+  DwtArgs a{};
+  IdwtArgs i{};
+  DeepArgs e{};
+};
+struct SideJobs {
+  SideJob first, second;  // analysis levels 1 and 2 (SIDE_DWT; second only if the deep levels start at 3)
+  SideJob deep;           // SIDE_DEEP
+  SideJob lower;          // synthesis level 2 (SIDE_IDWT; only with second)
+  SideJob top;            // finest synthesis level (SIDE_TOP)
+};
+// The jobs of sparsity_apply, each to run after the one before it; false if the dictionary has
+// other levels than they cover.
+bool side_jobs(const Sara& S, const float* x, float* s, float alpha, const float* wts, float* out, SideJobs& j);
+// The job `top` in a launch of its own.
+int side_top(const Sara& S, const SideJob& j, hipStream_t st);
 
 }  // namespace ri

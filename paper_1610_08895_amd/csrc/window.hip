@@ -27,6 +27,7 @@
 #include <algorithm>
 
 #include "plan.hpp"
+#include "sara_dev.hpp"
 
 namespace ri {
 
@@ -107,26 +108,43 @@ __device__ __forceinline__ int wave_scan(int v) {
 // the tile's own slot of the patch array (added to it with `add`), which nobody else writes:
 // no atomics and no order dependence, so results are deterministic.  The adjoint column pass
 // adds the overlapping regions.
-template <int MODE, int SPLIT>
+// SIDE: the workgroups after the tiles' are those of a sparsity job.
+template <int MODE, int SPLIT, bool SIDE>
 __global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restrict__ tiles, const int* __restrict__ list, int nlist,
                                                                  const int* __restrict__ woff, const int4* __restrict__ wsegs,
                                                                  const uint8_t* __restrict__ mask, int only,
                                                                  const unsigned* __restrict__ coord, float2* __restrict__ patch, KBPoly P,
                                                                  const float* __restrict__ y, const float* __restrict__ e,
-                                                                 float* __restrict__ v, const float* __restrict__ shrink, int add) {
-  // the data branch's kernels issue ahead of the sparsity branch's waves sharing their SIMDs
-  __builtin_amdgcn_s_setprio(3);
+                                                                 float* __restrict__ v, const float* __restrict__ shrink, int add, int stride,
+                                                                 SideJob side) {
   constexpr int NW = 4 * SPLIT, GT = 64 * NW;
   constexpr int DP = WROWS + 1;  // pitch of a window's patch in LDS
   static_assert(WROWS * DP * 2 <= WBUF, "a window's patch takes the place of its weights");
-  __shared__ __align__(16) float wbuf[NW][WBUF];
-  __shared__ __align__(16) float vbuf[NW][2 * CH];
-  __shared__ int4 tab[NW][64];
-  __shared__ int touched[NW];
+  struct Shared {
+    float wbuf[NW][WBUF];
+    float vbuf[NW][2 * CH];
+    int4 tab[NW][64];
+    int touched[NW];
+  };
+  constexpr int SIDE_BYTES = SIDE ? side_smem<GT>() : 0;
+  __shared__ __align__(16) char smem[SIDE_BYTES > int(sizeof(Shared)) ? SIDE_BYTES : int(sizeof(Shared))];
+  if constexpr (SIDE) {
+    if (int(blockIdx.x) >= stride) {
+      side_body<GT, SIDE_DEEP>(side, int(blockIdx.x) - stride, smem);
+      return;
+    }
+  }
+  // the data branch's kernels issue ahead of the sparsity branch's waves sharing their SIMDs
+  __builtin_amdgcn_s_setprio(3);
+  Shared& sh = *reinterpret_cast<Shared*>(smem);
+  auto& wbuf = sh.wbuf;
+  auto& vbuf = sh.vbuf;
+  auto& tab = sh.tab;
+  auto& touched = sh.touched;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, m = lane & 15, comp = g & 1, sl = lane_vis(lane);
   float* w = wbuf[wv];
-  for (int b = blockIdx.x; b < nlist; b += gridDim.x) {
+  for (int b = blockIdx.x; b < nlist; b += stride) {
     const int u = list != nullptr ? list[b] : b;
     const int win = wv / SPLIT, first = (wv % SPLIT) * CH;
     const int s0 = woff[4 * u + win], s1 = woff[4 * u + win + 1];
@@ -140,14 +158,14 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restri
       if (act && mask != nullptr) act = mask[sg.z] != 0;
       if (only >= 0) act = act && sg.z == only;
       const int cnt = act ? sg.y : 0;
-      float sh = 0.f;
-      if (MODE != GR_APPLY && act) sh = shrink[sg.z];
+      float fac = 0.f;
+      if (MODE != GR_APPLY && act) fac = shrink[sg.z];
       const int incl = wave_scan(cnt);
       const int total = __builtin_amdgcn_readlane(incl, 63);
       if (total == 0) continue;
       any = true;
       wave_lds_fence();
-      tab[wv][lane] = make_int4(incl - cnt, sg.x, __float_as_int(sh), sg.w);
+      tab[wv][lane] = make_int4(incl - cnt, sg.x, __float_as_int(fac), sg.w);
       wave_lds_fence();
       int step0 = 0;  // the largest power of two below nb
       if (nb > 1) step0 = 1 << (31 - __builtin_clz(nb - 1));
@@ -252,11 +270,23 @@ float* words(float2* p) { return reinterpret_cast<float*>(p); }
 
 template <int MODE, int SPLIT>
 int launch(const Plan& p, const int* list, int nlist, const uint8_t* mask, int only, float2* patch, const float2* y,
-           const float2* e, float2* v, const float* shrink, bool add, hipStream_t s) {
+           const float2* e, float2* v, const float* shrink, bool add, hipStream_t s, const SideJob* side) {
   const int g = p.persistent_wgs > 0 ? std::min(p.persistent_wgs, nlist) : nlist;
-  hipLaunchKernelGGL((k_win_grid<MODE, SPLIT>), dim3(g), dim3(256 * SPLIT), 0, s, p.gtiles, list, nlist, p.woff,
-                     p.wsegs, mask, only, reinterpret_cast<const unsigned*>(p.coord), patch, p.poly, words(y),
-                     words(e), words(v), shrink, add ? 1 : 0);
+  const unsigned* coord = reinterpret_cast<const unsigned*>(p.coord);
+  if (side != nullptr && side->wgs > 0) {
+    if constexpr (SPLIT == 4 && MODE != GR_APPLY) {
+      static_assert(256 * SPLIT == DEEP_THREADS, "the job's workgroup size");
+      hipLaunchKernelGGL((k_win_grid<MODE, SPLIT, true>), dim3(g + side->wgs), dim3(256 * SPLIT), 0, s, p.gtiles,
+                         list, nlist, p.woff, p.wsegs, mask, only, coord, patch, p.poly, words(y), words(e),
+                         words(v), shrink, add ? 1 : 0, g, *side);
+    } else {
+      return fail(RI_EINVAL, "windowed gridding: no side job here");
+    }
+  } else {
+    hipLaunchKernelGGL((k_win_grid<MODE, SPLIT, false>), dim3(g), dim3(256 * SPLIT), 0, s, p.gtiles, list, nlist,
+                       p.woff, p.wsegs, mask, only, coord, patch, p.poly, words(y), words(e), words(v), shrink,
+                       add ? 1 : 0, g, SideJob{});
+  }
   RI_LAUNCH_CHECK();
   return RI_OK;
 }
@@ -265,10 +295,11 @@ int launch(const Plan& p, const int* list, int nlist, const uint8_t* mask, int o
 // them, so that a fresh pass also clears what the DDE kernels may have left there).
 template <int MODE>
 int grid_tiles(const Plan& p, const int* list, int nlist, const uint8_t* mask, int only, float2* patch,
-               const float2* y, const float2* e, float2* v, const float* shrink, bool add, hipStream_t s) {
+               const float2* y, const float2* e, float2* v, const float* shrink, bool add, hipStream_t s,
+               const SideJob* side = nullptr) {
   if (nlist <= 0) return RI_OK;
-  return p.win_split == 1 ? launch<MODE, 1>(p, list, nlist, mask, only, patch, y, e, v, shrink, add, s)
-                          : launch<MODE, 4>(p, list, nlist, mask, only, patch, y, e, v, shrink, add, s);
+  return p.win_split == 1 ? launch<MODE, 1>(p, list, nlist, mask, only, patch, y, e, v, shrink, add, s, side)
+                          : launch<MODE, 4>(p, list, nlist, mask, only, patch, y, e, v, shrink, add, s, side);
 }
 
 }  // namespace
@@ -278,12 +309,13 @@ int win_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* patch
 }
 
 int win_project(const Plan& p, const float2* e, float2* v, const float* shrink, const uint8_t* mask, float2* patch,
-                hipStream_t s) {
-  return grid_tiles<GR_PROJECT>(p, nullptr, p.n_gtiles, mask, -1, patch, nullptr, e, v, shrink, true, s);
+                hipStream_t s, const SideJob* side) {
+  return grid_tiles<GR_PROJECT>(p, nullptr, p.n_gtiles, mask, -1, patch, nullptr, e, v, shrink, true, s, side);
 }
 
-int win_project_all(const Plan& p, const float2* r, float2* v, const float* shrink, float2* patch, hipStream_t s) {
-  return grid_tiles<GR_FRESH>(p, nullptr, p.n_gtiles, nullptr, -1, patch, nullptr, r, v, shrink, false, s);
+int win_project_all(const Plan& p, const float2* r, float2* v, const float* shrink, float2* patch, hipStream_t s,
+                    const SideJob* side) {
+  return grid_tiles<GR_FRESH>(p, nullptr, p.n_gtiles, nullptr, -1, patch, nullptr, r, v, shrink, false, s, side);
 }
 
 int win_project_block(const Plan& p, int block, const float2* e, float2* v, const float* shrink, float2* patch,
