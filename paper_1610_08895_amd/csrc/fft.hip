@@ -22,15 +22,19 @@ __device__ __forceinline__ int pix_of(int q, int n, int K) {
   return q < n / 2 ? q + n / 2 : (q >= K - n / 2 ? q - K + n / 2 : -1);
 }
 
+// Grids of up to 1024 cells take the smallest panels that fill a wavefront with radix-8 jobs (rows)
+// or four columns (a 32-byte segment of a row): their passes are as long as one workgroup's
+// chain of passes, and more workgroups shorten it: forward columns 9.7 -> 7.6 us at K = 1024 (64
+// -> 256 workgroups), 7.0 -> 5.6 at 512 (32 -> 128); the rows keep their 3 to 6 us.
 template <int K>
 struct RowCfg {
-  static constexpr int W = (K / 2 < 2048 / K ? K / 2 : (2048 / K > 1 ? 2048 / K : 1));
-  static constexpr int NT = K == 32 ? 64 : (K == 4096 ? 512 : 256);
+  static constexpr int W = K > WINDOWED_K ? 1 : (K >= 512 ? 1 : (512 / K < K / 2 ? 512 / K : K / 2));
+  static constexpr int NT = K == 4096 ? 512 : (K > WINDOWED_K ? 256 : (W * K / 8 < 64 ? 64 : W * K / 8));
 };
 template <int K>
 struct ColCfg {
-  static constexpr int W = K <= 1024 ? 16 : 16384 / K;
-  static constexpr int NT = K <= 512 ? 256 : 512;
+  static constexpr int W = K <= WINDOWED_K ? 4 : 16384 / K;
+  static constexpr int NT = K > WINDOWED_K ? 512 : (W * K / 16 < 64 ? 64 : W * K / 16);
 };
 
 // Adjoint column panels of windowed plans.  Up to SIDE_K a sparsity job may ride on the launch
