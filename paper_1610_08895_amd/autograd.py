@@ -93,11 +93,11 @@ class _UnrolledPD(torch.autograd.Function):
         for t in range(T):
             if t % checkpoint == 0:
                 pd.refresh()  # the segment re-run starts from the same running sum
-                saved[t] = [pd.get(w).clone() for w in (L.RI_PD_X, L.RI_PD_XTILDE, L.RI_PD_S, L.RI_PD_V)]
+                saved[t] = [pd.get(w) for w in (L.RI_PD_X, L.RI_PD_XTILDE, L.RI_PD_S, L.RI_PD_V)]
             pd.step(masks[t])
         ctx.pd, ctx.saved, ctx.masks, ctx.checkpoint = pd, saved, masks, checkpoint
         ctx.params_device, ctx.params_dtype = params.device, params.dtype
-        return pd.get(L.RI_PD_X).clone()
+        return pd.get(L.RI_PD_X)
 
     @staticmethod
     def backward(ctx, gx):
@@ -115,8 +115,8 @@ class _UnrolledPD(torch.autograd.Function):
             tape = []
             for t in range(t0, min(t0 + C, T)):
                 pd.step(masks[t], stats)
-                tape.append((masks[t], pd.get(L.RI_PD_X).clone(), pd.get(L.RI_PD_S).clone(),
-                             pd.get(L.RI_PD_V).clone(), pd.get(L.RI_PD_E).clone(), stats.clone()))
+                tape.append((masks[t], pd.get(L.RI_PD_X), pd.get(L.RI_PD_S), pd.get(L.RI_PD_V), pd.get(L.RI_PD_E),
+                             stats.clone()))
             for rec in reversed(tape):
                 pd.step_vjp(*rec, xbar, xtbar, sbar, vbar, pgrad)
         grad = pgrad.to(device=ctx.params_device, dtype=ctx.params_dtype)
