@@ -7,20 +7,23 @@
 //
 //   W_m[ty][tx] = sum_{p,q} d_m[q, p] w_y[ty - h - q] w_x[tx - h - p],   0 <= tx, ty < S,
 //
-// on the S = J + 2h cells per axis starting at floor(kappa) - J/2 + 1 - h.  The weights are
-// built once per plan (k_dde_weights) and stored tap-major, w[t * M + m], so the 64 lanes of
-// a wavefront, which take 64 consecutive visibilities, read 512 contiguous bytes per tap:
-// with S^2 complex weights per visibility (1152 bytes at S = 12) against 24 bytes of
-// coordinates and data, these operators are bound by streaming the weights from HBM.
+// on the S = J + 2h cells per axis starting at floor(kappa) - J/2 + 1 - h.  The S^2 weights are
+// never stored: streaming them bound both directions to HBM (1152 bytes per visibility at
+// S = 12), while the 25 taps they come from are 200 bytes, and the sum over p, q and the kernel's
+// taps separates into about 1500 multiply-adds, 91 cycles of a SIMD.  The taps are stored
+// tap-major, d[t * M + m], so the 64 lanes of a wavefront, which take 64 consecutive visibilities,
+// read 512 contiguous bytes per tap.  300007 visibilities, 512^2 image, jd = 5, 16 blocks: G 131 us
+// with stored weights, 30 without (13 of multiply-adds); its adjoint 148 and 41 us (15 of
+// multiply-adds, about as much of LDS atomics), merging the patches 19 and 16 us.
 //
 // Degridding stages a tile plus the kernel's reach in LDS, as the plain kernel does, and
-// forms y_m = sum_t W_m[t] b[cell_m + t].  Gridding (the adjoint, conjugate weights) is
-// owner-computes per tile: one workgroup accumulates every active item of its tile exactly
-// in fixed point with 64-bit LDS integer atomics (per item a power-of-two scale from the
-// bound sum_m max_t(|Re W| + |Im W|) (|Re v| + |Im v|)), folds each item into FP32
-// registers, and writes the tile's whole region (tile plus reach) to a per-tile patch; a
-// merge pass then adds, for every grid cell, the patches of the up to nine tiles whose
-// regions cover it, in a fixed order.  Results are deterministic.
+// forms y_m = sum_{q,p} d_m[q, p] (sum of the kernel's taps shifted by (q, p)).  Gridding (the
+// adjoint, conjugate weights) is owner-computes per unit of a tile's items: one workgroup
+// accumulates up to MAX_BIN visibilities at a time exactly in fixed point with 64-bit LDS integer
+// atomics (a power-of-two scale from the bound sum_m max_t(|Re W| + |Im W|) (|Re v| + |Im v|)),
+// and writes the tile's whole region (tile plus reach) to the unit's patch; a merge pass then
+// adds, for every grid cell, the patches of the up to four tiles whose regions cover it, in a
+// fixed order.  Results are deterministic.
 #include <algorithm>
 #include <cmath>
 #include <new>
@@ -32,8 +35,9 @@ namespace ri {
 namespace {
 
 constexpr int DT = 256;                 // threads per workgroup
-constexpr int DNV = MAX_BIN / DT;       // visibilities per thread per item
+constexpr int DNV = MAX_BIN / DT;       // visibilities per thread per item (degridding)
 constexpr int MAX_H = 3;                // jd <= 7
+constexpr int GRID_UNIT_VIS = 512;      // visibilities of a gridding unit, if M is not larger than 2^19
 
 template <int T, int H>
 struct DdeGeom {
@@ -43,48 +47,56 @@ struct DdeGeom {
   static constexpr int TP = TW + 1;            // LDS pitch
 };
 
-// One thread per visibility: W = d * (w_y (x) w_x) by separable convolution, and its bound.
+// The tap polynomials' row ty of W for taps d (any factor included): e[p] = sum_q w_y[ty - q] d[q][p],
+// then row[tx] = init + sum_p w_x[tx - p] e[p].  ty is a constant where this is unrolled.
 template <int H>
-__global__ __launch_bounds__(DT) void k_dde_weights(int64_t M, const uint2* __restrict__ coord,
-                                                    const float2* __restrict__ d, KBPoly P,
-                                                    float2* __restrict__ w, float* __restrict__ wmax) {
+__device__ __forceinline__ void weight_row(int ty, const float* wx, const float* wy, const float2* d, float init,
+                                           float2* row) {
+  constexpr int JD = 2 * H + 1, S = KB_J + 2 * H;
+#pragma unroll
+  for (int tx = 0; tx < S; ++tx) row[tx] = make_float2(init, init);
+#pragma unroll
+  for (int p = 0; p < JD; ++p) {
+    float2 e = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int q = 0; q < JD; ++q) {
+      if (ty - q < 0 || ty - q >= KB_J) continue;
+      e.x = fmaf(wy[ty - q], d[q * JD + p].x, e.x);
+      e.y = fmaf(wy[ty - q], d[q * JD + p].y, e.y);
+    }
+#pragma unroll
+    for (int j = 0; j < KB_J; ++j) {
+      row[j + p].x = fmaf(wx[j], e.x, row[j + p].x);
+      row[j + p].y = fmaf(wx[j], e.y, row[j + p].y);
+    }
+  }
+}
+
+// One thread per visibility: its taps into tap-major order, and the bound of its weights,
+// max over the taps of |Re W| + |Im W|.
+template <int H>
+__global__ __launch_bounds__(DT) void k_dde_taps(int64_t M, const uint2* __restrict__ coord,
+                                                 const float2* __restrict__ in, KBPoly P, float2* __restrict__ taps,
+                                                 float* __restrict__ wmax) {
   constexpr int JD = 2 * H + 1, S = KB_J + 2 * H;
   for (int64_t m = blockIdx.x * int64_t(DT) + threadIdx.x; m < M; m += int64_t(gridDim.x) * DT) {
     float wx[KB_J], wy[KB_J];
     int cx, cy;
     kb_weights(coord[m].x, P, wx, cx);
     kb_weights(coord[m].y, P, wy, cy);
-    const float2* dm = d + m * JD * JD;
+    float2 d[JD * JD];
+#pragma unroll
+    for (int t = 0; t < JD * JD; ++t) {
+      d[t] = in[m * (JD * JD) + t];
+      taps[size_t(t) * M + m] = d[t];
+    }
     float mx = 0.f;
-    // every loop has a compile-time trip count and is unrolled, so all register indices are
-    // constants: W[ty][tx] = sum_{q,p} d[q][p] w_y[ty - q] w_x[tx - p] (shifts q - H, p - H)
 #pragma unroll
     for (int ty = 0; ty < S; ++ty) {
       float2 row[S];
+      weight_row<H>(ty, wx, wy, d, 0.f, row);
 #pragma unroll
-      for (int tx = 0; tx < S; ++tx) row[tx] = make_float2(0.f, 0.f);
-#pragma unroll
-      for (int q = 0; q < JD; ++q) {
-        const int jy = ty - q;  // the Kaiser-Bessel row of this term
-        if (jy < 0 || jy >= KB_J) continue;
-        const float a = wy[jy];
-#pragma unroll
-        for (int pp = 0; pp < JD; ++pp) {
-          const float2 dq = dm[q * JD + pp];
-          const float2 c = make_float2(a * dq.x, a * dq.y);
-#pragma unroll
-          for (int jx = 0; jx < KB_J; ++jx) {
-            const int tx = jx + pp;  // < S
-            row[tx].x = fmaf(c.x, wx[jx], row[tx].x);
-            row[tx].y = fmaf(c.y, wx[jx], row[tx].y);
-          }
-        }
-      }
-#pragma unroll
-      for (int tx = 0; tx < S; ++tx) {
-        w[size_t(ty * S + tx) * M + m] = row[tx];
-        mx = fmaxf(mx, fabsf(row[tx].x) + fabsf(row[tx].y));
-      }
+      for (int tx = 0; tx < S; ++tx) mx = fmaxf(mx, fabsf(row[tx].x) + fabsf(row[tx].y));
     }
     wmax[m] = mx;
   }
@@ -97,12 +109,12 @@ enum { DD_APPLY = 0, DD_RESIDUAL = 1 };
 template <int T, int H, int MODE>
 __global__ __launch_bounds__(DT) void k_degrid_dde(const int4* __restrict__ units, int nunits,
                                                    const Item* __restrict__ items, const uint8_t* __restrict__ mask,
-                                                   const uint2* __restrict__ coord, const float2* __restrict__ w,
-                                                   int64_t M, const float2* __restrict__ grid, int K, int tpa,
+                                                   const uint2* __restrict__ coord, const float2* __restrict__ taps,
+                                                   int64_t M, KBPoly P, const float2* __restrict__ grid, int K, int tpa,
                                                    float2* __restrict__ out, const float2* __restrict__ y,
                                                    const float2* __restrict__ v, double* __restrict__ part) {
   using G = DdeGeom<T, H>;
-  constexpr int S = G::S, TW = G::TW, TP = G::TP, R0 = G::R0;
+  constexpr int S = G::S, TW = G::TW, TP = G::TP, R0 = G::R0, JD = 2 * H + 1;
   constexpr int NWV = DT / 64;
   __shared__ float2 tile[TW * TP];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -122,27 +134,54 @@ __global__ __launch_bounds__(DT) void k_degrid_dde(const int4* __restrict__ unit
       const Item it = items[q];
       if (mask != nullptr && mask[it.x] == 0) continue;
       double sr = 0.0, se = 0.0;
+      const int rw = (wv + q) & (NWV - 1);  // items are often short: their first wavefronts rotate
       for (int k = 0; k < DNV; ++k) {
-        const int s = threadIdx.x + k * DT;
+        const int s = rw * 64 + lane + k * DT;
         if (s >= it.w) break;
         const int64_t m = it.z + s;
         const uint2 c = coord[m];
+        float wx[KB_J], wy[KB_J];
+        int cx, cy;
+        kb_weights(c.x, P, wx, cx);
+        kb_weights(c.y, P, wy, cy);
         // region row / column of the first tap: cell - 3 - h - (tile origin - R0)
-        const int ly0 = int(c.y >> FRAC_BITS) - ty * T, lx0 = int(c.x >> FRAC_BITS) - tx * T;
-        const float2* base = &tile[ly0 * TP + lx0];
-        const float2* wm = w + m;
-        float2 acc = make_float2(0.f, 0.f);
+        const float2* base = &tile[(cy - ty * T) * TP + (cx - tx * T)];
+        // vs[q][p]: the kernel's sum at shift (q, p)
+        float2 vs[JD][JD];
+#pragma unroll
+        for (int q = 0; q < JD; ++q)
+#pragma unroll
+          for (int p = 0; p < JD; ++p) vs[q][p] = make_float2(0.f, 0.f);
+#pragma unroll
         for (int a = 0; a < S; ++a) {
-          float2 wr[S];
+          float2 row[S];
 #pragma unroll
-          for (int b = 0; b < S; ++b) wr[b] = wm[size_t(a * S + b) * M];
+          for (int b = 0; b < S; ++b) row[b] = base[a * TP + b];
 #pragma unroll
-          for (int b = 0; b < S; ++b) {
-            const float2 g = base[a * TP + b];
-            acc.x = fmaf(wr[b].x, g.x, fmaf(-wr[b].y, g.y, acc.x));
-            acc.y = fmaf(wr[b].x, g.y, fmaf(wr[b].y, g.x, acc.y));
+          for (int p = 0; p < JD; ++p) {
+            float2 t = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int j = 0; j < KB_J; ++j) {
+              t.x = fmaf(wx[j], row[j + p].x, t.x);
+              t.y = fmaf(wx[j], row[j + p].y, t.y);
+            }
+#pragma unroll
+            for (int q = 0; q < JD; ++q) {
+              if (a - q < 0 || a - q >= KB_J) continue;
+              vs[q][p].x = fmaf(wy[a - q], t.x, vs[q][p].x);
+              vs[q][p].y = fmaf(wy[a - q], t.y, vs[q][p].y);
+            }
           }
         }
+        float2 acc = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int q = 0; q < JD; ++q)
+#pragma unroll
+          for (int p = 0; p < JD; ++p) {
+            const float2 d = taps[size_t(q * JD + p) * M + m];
+            acc.x = fmaf(d.x, vs[q][p].x, fmaf(-d.y, vs[q][p].y, acc.x));
+            acc.y = fmaf(d.x, vs[q][p].y, fmaf(d.y, vs[q][p].x, acc.y));
+          }
         if (MODE == DD_APPLY) {
           out[m] = acc;
         } else {
@@ -158,8 +197,8 @@ __global__ __launch_bounds__(DT) void k_degrid_dde(const int4* __restrict__ unit
         sr = wave_sum(sr);
         se = wave_sum(se);
         if (lane == 0) {
-          part[(size_t(it.y) * NWV + wv) * 2] = sr;
-          part[(size_t(it.y) * NWV + wv) * 2 + 1] = se;
+          part[(size_t(it.y) * NWV + rw) * 2] = sr;
+          part[(size_t(it.y) * NWV + rw) * 2 + 1] = se;
         }
       }
     }
@@ -167,54 +206,80 @@ __global__ __launch_bounds__(DT) void k_degrid_dde(const int4* __restrict__ unit
   }
 }
 
-// Gridding with conjugate DDE weights over whole-tile units.  PROJECT: the values are the
-// step-8 dual changes (v_new = r shrink_i stored, v_new - v_old gridded), else y.
-// The tile's region goes to its patch (stored, or added with ADDP).
+// Gridding with conjugate DDE weights over units of one tile's items {tile, first, end, patch}.
+// PROJECT: the values are the step-8 dual changes (v_new = r shrink_i stored, v_new - v_old
+// gridded), else y.  The tile's region goes to the unit's patch (stored), or is added to the
+// tile's (ADDP; each tile then has one unit).  A unit is taken in groups of items of at most
+// MAX_BIN visibilities: the wavefronts take the active items in turn, list their visibilities
+// without gaps, and sum the fixed-point bound; the group's threads then take the list.  An item
+// at a time, as a block's part of a tile comes, left most of a workgroup idle (blocks cut a tile
+// into pieces of a few dozen visibilities): 160 us, at 300007 visibilities and jd = 5, against 73
+// in list order and 49 with a wavefront's lanes spread over the list; 41 with room for all taps
+// of a visibility in registers at once (3 wavefronts per SIMD instead of 4).
 template <int T, int H, bool PROJECT, bool ADDP>
-__global__ __launch_bounds__(DT) void k_grid_dde(const int4* __restrict__ units, int nunits,
+__global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __restrict__ units, int nunits,
                                                  const Item* __restrict__ items, const uint8_t* __restrict__ mask,
-                                                 const uint2* __restrict__ coord, const float2* __restrict__ w,
-                                                 const float* __restrict__ wmax, int64_t M,
+                                                 const uint2* __restrict__ coord, const float2* __restrict__ taps,
+                                                 const float* __restrict__ wmax, int64_t M, KBPoly P,
                                                  const float2* __restrict__ y, const float2* __restrict__ e,
                                                  float2* __restrict__ v, const float* __restrict__ shrink,
                                                  float2* __restrict__ patch, int tpa) {
   using G = DdeGeom<T, H>;
-  constexpr int S = G::S, TW = G::TW, TP = G::TP;
+  constexpr int S = G::S, TW = G::TW, TP = G::TP, JD = 2 * H + 1;
   constexpr int NWV = DT / 64;
-  constexpr int NC = (TW * TW + DT - 1) / DT;
   __shared__ unsigned long long acci[TW * TP];
+  __shared__ float2 val[MAX_BIN];
+  __shared__ int vis[MAX_BIN];
   __shared__ float red[NWV];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   for (int k = threadIdx.x; k < TW * TP; k += DT) acci[k] = 0ull;
-  __syncthreads();
   for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
     const int4 un = units[u];
     const int ty = un.x / tpa, tx = un.x - (un.x / tpa) * tpa;
-    float2 acc[NC];
-#pragma unroll
-    for (int j = 0; j < NC; ++j) acc[j] = make_float2(0.f, 0.f);
-    for (int q = un.y; q < un.z; ++q) {
-      const Item it = items[q];
-      if (mask != nullptr && mask[it.x] == 0) continue;
-      float2 val[DNV];
+    float2* pt = patch + size_t(ADDP ? un.x : un.w) * TW * TW;
+    bool first = !ADDP;
+    for (int q = un.y; q < un.z || first;) {
+      // list the group's visibilities; every wavefront scans the items' widths
+      int cnt = 0;
       float babs = 0.f;
-#pragma unroll
-      for (int k = 0; k < DNV; ++k) {
-        const int s = threadIdx.x + k * DT;
-        val[k] = make_float2(0.f, 0.f);
-        if (s < it.w) {
-          const int64_t m = it.z + s;
-          if (PROJECT) {
-            const float sh = shrink[it.x];
-            const float2 vo = v[m], rr = e[m];  // r = v_old + G b - y from the degridding
-            const float2 vn = make_float2(rr.x * sh, rr.y * sh);
-            v[m] = vn;
-            val[k] = make_float2(vn.x - vo.x, vn.y - vo.y);
-          } else {
-            val[k] = y[m];
-          }
-          babs += wmax[m] * (fabsf(val[k].x) + fabsf(val[k].y));
+      for (bool full = false; q < un.z && !full;) {
+        const int have = min(64, un.z - q);
+        Item it{};
+        int w = 0;
+        if (lane < have) {
+          it = items[q + lane];
+          w = mask == nullptr || mask[it.x] != 0 ? it.w : 0;
         }
+        int end = w;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int t = __shfl_up(end, o);
+          if (lane >= o) end += t;
+        }
+        const int fit = __popcll(__ballot(lane < have && cnt + end <= MAX_BIN));
+        full = fit < have;
+        for (int i = wv; i < fit; i += NWV) {
+          const int iw = __shfl(w, i), im = __shfl(it.z, i), s0 = cnt + __shfl(end, i) - iw;
+          const float sh = PROJECT && iw > 0 ? shrink[__shfl(it.x, i)] : 0.f;
+#pragma unroll 1
+          for (int s = lane; s < iw; s += 64) {
+            const int64_t m = im + s;
+            float2 x;
+            if (PROJECT) {
+              const float2 vo = v[m], rr = e[m];  // r = v_old + G b - y from the degridding
+              const float2 vn = make_float2(rr.x * sh, rr.y * sh);
+              v[m] = vn;
+              x = make_float2(vn.x - vo.x, vn.y - vo.y);
+            } else {
+              x = y[m];
+            }
+            val[s0 + s] = x;
+            vis[s0 + s] = int(m);
+            babs += wmax[m] * (fabsf(x.x) + fabsf(x.y));
+          }
+        }
+        if (fit > 0) cnt += __shfl(end, fit - 1);
+        q += fit;
       }
       babs = wave_sum(babs);
       if (lane == 0) red[wv] = babs;
@@ -222,97 +287,127 @@ __global__ __launch_bounds__(DT) void k_grid_dde(const int4* __restrict__ units,
       float bound = 0.f;
 #pragma unroll
       for (int k = 0; k < NWV; ++k) bound += red[k];
+      float inv = 0.f;
       if (bound > 0.f) {
         // 2^E with bound * 2^E <= 2^30: no cell's sum of either part can leave 31 bits
         int ex = 0;
         frexpf(bound * 1.0001f, &ex);
         const float scale = ldexpf(1.f, 30 - ex);
-#pragma unroll
-        for (int k = 0; k < DNV; ++k) {
-          const int s = threadIdx.x + k * DT;
-          if (s >= it.w) continue;
-          const int64_t m = it.z + s;
+        inv = ldexpf(1.f, ex - 30);
+        // neighbours in the list share cells, which one instruction's atomics would take in turn: a
+        // wavefront's lanes take visibilities `nw` apart
+        const int nw = (cnt + 63) / 64;
+#pragma unroll 1
+        for (int w = wv; w < nw; w += NWV) {
+          const int s = lane * nw + w;
+          if (s >= cnt) continue;
+          const int64_t m = vis[s];
+          const float vr = val[s].x * scale, vi = val[s].y * scale;
           const uint2 c = coord[m];
-          const int ly0 = int(c.y >> FRAC_BITS) - ty * T, lx0 = int(c.x >> FRAC_BITS) - tx * T;
-          unsigned long long* base = &acci[ly0 * TP + lx0];
-          const float vr = val[k].x * scale, vi = val[k].y * scale;
-          const float2* wm = w + m;
-          for (int a = 0; a < S; ++a) {
-            float2 wr[S];
+          float2 d[JD * JD];  // conj(d) v
 #pragma unroll
-            for (int b = 0; b < S; ++b) wr[b] = wm[size_t(a * S + b) * M];
-#pragma unroll
-            for (int b = 0; b < S; ++b) {
-              // conj(W) v = (Wr Vr + Wi Vi) + i (Wr Vi - Wi Vr), rounded to nearest
-              const long long ir = static_cast<int>(floorf(fmaf(wr[b].x, vr, fmaf(wr[b].y, vi, 0.5f))));
-              const long long ii = static_cast<int>(floorf(fmaf(wr[b].x, vi, fmaf(-wr[b].y, vr, 0.5f))));
-              atomicAdd(base + a * TP + b, static_cast<unsigned long long>(ii * 4294967296LL + ir));
-            }
+          for (int t = 0; t < JD * JD; ++t) {
+            const float2 g = taps[size_t(t) * M + m];
+            d[t] = make_float2(fmaf(g.x, vr, g.y * vi), fmaf(g.x, vi, -g.y * vr));
           }
-        }
-        __syncthreads();
-        const float inv = ldexpf(1.f, ex - 30);
+          float wx[KB_J], wy[KB_J];
+          int cx, cy;
+          kb_weights(c.x, P, wx, cx);
+          kb_weights(c.y, P, wy, cy);
+          unsigned long long* base = &acci[(cy - ty * T) * TP + (cx - tx * T)];
 #pragma unroll
-        for (int j = 0; j < NC; ++j) {
-          const int c = threadIdx.x + j * DT;
-          if (c < TW * TW) {
-            unsigned long long* cell = &acci[c + c / TW];
-            const unsigned long long w64 = *cell;
-            if (w64) {
-              *cell = 0ull;
-              const int ir = static_cast<int>(static_cast<unsigned>(w64));
-              const int ii = static_cast<int>(static_cast<unsigned>(
-                  (w64 - static_cast<unsigned long long>(static_cast<long long>(ir))) >> 32));
-              acc[j].x += float(ir) * inv;
-              acc[j].y += float(ii) * inv;
+          for (int a = 0; a < S; ++a) {
+            float2 row[S];
+            weight_row<H>(a, wx, wy, d, 0.5f, row);
+#pragma unroll
+            for (int b = 0; b < S; ++b) {  // rounded to nearest
+              const int ir = static_cast<int>(floorf(row[b].x)), ii = static_cast<int>(floorf(row[b].y));
+              const unsigned hi = unsigned(ii) + unsigned(ir >> 31);
+              atomicAdd(base + a * TP + b, (static_cast<unsigned long long>(hi) << 32) | unsigned(ir));
             }
           }
         }
       }
       __syncthreads();
-    }
-    float2* pt = patch + size_t(un.x) * TW * TW;
-#pragma unroll
-    for (int j = 0; j < NC; ++j) {
-      const int c = threadIdx.x + j * DT;
-      if (c >= TW * TW) continue;
-      if (ADDP) {
-        if (acc[j].x != 0.f || acc[j].y != 0.f) {
-          const float2 o = pt[c];
-          pt[c] = make_float2(o.x + acc[j].x, o.y + acc[j].y);
+      if (first || bound > 0.f) {
+#pragma unroll 2
+        for (int c = threadIdx.x; c < TW * TW; c += DT) {
+          unsigned long long* cell = &acci[c + c / TW];
+          const unsigned long long w64 = *cell;
+          float2 x = make_float2(0.f, 0.f);
+          if (w64) {
+            *cell = 0ull;
+            const int ir = static_cast<int>(static_cast<unsigned>(w64));
+            const int ii = static_cast<int>(static_cast<unsigned>(
+                (w64 - static_cast<unsigned long long>(static_cast<long long>(ir))) >> 32));
+            x = make_float2(float(ir) * inv, float(ii) * inv);
+          }
+          if (first) {
+            pt[c] = x;
+          } else if (w64) {
+            const float2 o = pt[c];
+            pt[c] = make_float2(o.x + x.x, o.y + x.y);
+          }
         }
-      } else {
-        pt[c] = acc[j];
       }
+      first = false;
     }
   }
+}
+
+// The sum of the patches that cover cell (iy, ix) of tile (ty, tx): its own, and in each axis at
+// most one neighbour's (above or to the left of the near edge, below or to the right of the far
+// one).  All four are loaded, the absent ones from the own patch and dropped, so that no load
+// waits for another.  more: the further patches of tile t are [more[t], more[t + 1]) (NULL: none).
+template <int T, int H>
+__device__ __forceinline__ float2 covering(const float2* __restrict__ patch, const int* __restrict__ more, int tpa,
+                                           int ty, int tx, int iy, int ix) {
+  using G = DdeGeom<T, H>;
+  constexpr int TW = G::TW, R0 = G::R0, NEAR = TW - T - R0, FAR = T - R0;
+  static_assert(NEAR <= FAR, "one neighbour per axis");
+  const int dy = iy < NEAR ? -1 : (iy >= FAR ? 1 : 0), dx = ix < NEAR ? -1 : (ix >= FAR ? 1 : 0);
+  const int ny = (ty + dy + tpa) & (tpa - 1), nx = (tx + dx + tpa) & (tpa - 1);
+  const int oy = iy + R0, ox = ix + R0;
+  const int t[4] = {ty * tpa + tx, ty * tpa + nx, ny * tpa + tx, ny * tpa + nx};
+  const int o[4] = {oy * TW + ox, oy * TW + ox - dx * T, (oy - dy * T) * TW + ox, (oy - dy * T) * TW + ox - dx * T};
+  const bool on[4] = {true, dx != 0, dy != 0, dx != 0 && dy != 0};
+  float2 a[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) a[k] = patch[size_t(on[k] ? t[k] : t[0]) * TW * TW + (on[k] ? o[k] : o[0])];
+  if (more != nullptr) {
+    int f[4], n[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      f[k] = more[t[k]];
+      n[k] = on[k] ? more[t[k] + 1] - f[k] : 0;
+    }
+    const int most = max(max(n[0], n[1]), max(n[2], n[3]));
+    for (int j = 0; j < most; ++j) {
+      float2 x[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = patch[size_t(j < n[k] ? f[k] + j : t[k]) * TW * TW + (on[k] ? o[k] : o[0])];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (j < n[k]) a[k] = cadd(a[k], x[k]);
+    }
+  }
+  float2 s = a[0];
+#pragma unroll
+  for (int k = 1; k < 4; ++k)
+    if (on[k]) s = cadd(s, a[k]);
+  return s;
 }
 
 // grid cell (=, or += with ADD) the sum of the patches of the tiles whose regions cover
 // it, neighbours in a fixed order; one workgroup per tile.
 template <int T, int H, bool ADD>
 __global__ __launch_bounds__(DT) void k_dde_merge(float2* __restrict__ grid, const float2* __restrict__ patch,
-                                                  const uint8_t* __restrict__ tile_has, int K, int tpa) {
-  using G = DdeGeom<T, H>;
-  constexpr int TW = G::TW, R0 = G::R0;
-  static_assert(TW - R0 <= 2 * T && R0 <= T, "a region reaches into the neighbouring tiles only");
+                                                  const int* __restrict__ more, int K, int tpa) {
   const int t = blockIdx.x;
   const int ty = t / tpa, tx = t - (t / tpa) * tpa;
   for (int k = threadIdx.x; k < T * T; k += DT) {
     const int iy = k / T, ix = k - (k / T) * T;
-    float2 acc = make_float2(0.f, 0.f);
-#pragma unroll
-    for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int ly = iy - dy * T + R0, lx = ix - dx * T + R0;
-        if (ly < 0 || ly >= TW || lx < 0 || lx >= TW) continue;
-        const int nt = ((ty + dy + tpa) & (tpa - 1)) * tpa + ((tx + dx + tpa) & (tpa - 1));
-        if (!tile_has[nt]) continue;
-        const float2 h = patch[size_t(nt) * TW * TW + ly * TW + lx];
-        acc.x += h.x;
-        acc.y += h.y;
-      }
+    const float2 acc = covering<T, H>(patch, more, tpa, ty, tx, iy, ix);
     float2* g = &grid[size_t(ty * T + iy) * K + tx * T + ix];
     if (!ADD) {
       *g = acc;
@@ -329,33 +424,17 @@ __global__ __launch_bounds__(DT) void k_dde_merge(float2* __restrict__ grid, con
 // gridding tile.
 template <int T, int H, bool ADD>
 __global__ __launch_bounds__(DT) void k_dde_merge_win(float2* __restrict__ sum, const float2* __restrict__ patch,
-                                                  const uint8_t* __restrict__ tile_has, int K, int tpa, int gta) {
-  using G = DdeGeom<T, H>;
-  constexpr int TW = G::TW, R0 = G::R0;
-  static_assert(TW - R0 <= 2 * T && R0 <= T, "a region reaches into the neighbouring tiles only");
+                                                      const int* __restrict__ more, int K, int tpa, int gta) {
   const int gty = blockIdx.x / gta, gtx = blockIdx.x - (blockIdx.x / gta) * gta;
   float2* out = sum + size_t(blockIdx.x) * PATCH_CELLS;
-  for (int k = threadIdx.x; k < PATCH_CELLS; k += DT) {
-    const int R = k / PATCH_W, C = k - (k / PATCH_W) * PATCH_W;
-    if (R >= GSIDE || C >= GSIDE) {
-      if (!ADD) out[k] = make_float2(0.f, 0.f);
-      continue;
-    }
+  if (!ADD)
+    for (int k = threadIdx.x; k < PATCH_CELLS; k += DT)
+      if (k / PATCH_W >= GSIDE || k % PATCH_W >= GSIDE) out[k] = make_float2(0.f, 0.f);
+  for (int i = threadIdx.x; i < GSIDE * GSIDE; i += DT) {
+    const int R = i / GSIDE, C = i % GSIDE, k = R * PATCH_W + C;
     const int gy = (gty * GSIDE - (KB_J / 2 - 1) + R) & (K - 1), gx = (gtx * GSIDE - (KB_J / 2 - 1) + C) & (K - 1);
     const int ty = gy / T, iy = gy % T, tx = gx / T, ix = gx % T;
-    float2 acc = make_float2(0.f, 0.f);
-#pragma unroll
-    for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int ly = iy - dy * T + R0, lx = ix - dx * T + R0;
-        if (ly < 0 || ly >= TW || lx < 0 || lx >= TW) continue;
-        const int nt = ((ty + dy + tpa) & (tpa - 1)) * tpa + ((tx + dx + tpa) & (tpa - 1));
-        if (!tile_has[nt]) continue;
-        const float2 h = patch[size_t(nt) * TW * TW + ly * TW + lx];
-        acc.x += h.x;
-        acc.y += h.y;
-      }
+    const float2 acc = covering<T, H>(patch, more, tpa, ty, tx, iy, ix);
     if (!ADD) {
       out[k] = acc;
     } else if (acc.x != 0.f || acc.y != 0.f) {
@@ -398,11 +477,11 @@ size_t region_cells(const Plan& p) {
 }  // namespace
 
 void dde_destroy(Dde& dd) {
-  dev_free(dd.w);
+  dev_free(dd.taps);
   dev_free(dd.wmax);
   dev_free(dd.tunits);
+  dev_free(dd.more);
   dev_free(dd.patch);
-  dev_free(dd.tile_has);
   dd = Dde{};
 }
 
@@ -413,10 +492,10 @@ int dde_degrid(const Plan& p, const int4* units, int nunits, const Item* items, 
   return dispatch(p, [&]<int T, int H>() -> int {
     if (resid)
       hipLaunchKernelGGL((k_degrid_dde<T, H, DD_RESIDUAL>), dim3(wgs(p, nunits)), dim3(DT), 0, s, units, nunits,
-                         items, mask, p.coord, p.dde.w, p.M, grid, p.K, p.tpa, out, y, v, part);
+                         items, mask, p.coord, p.dde.taps, p.M, p.poly, grid, p.K, p.tpa, out, y, v, part);
     else
       hipLaunchKernelGGL((k_degrid_dde<T, H, DD_APPLY>), dim3(wgs(p, nunits)), dim3(DT), 0, s, units, nunits, items,
-                         mask, p.coord, p.dde.w, p.M, grid, p.K, p.tpa, out, y, v, part);
+                         mask, p.coord, p.dde.taps, p.M, p.poly, grid, p.K, p.tpa, out, y, v, part);
     RI_LAUNCH_CHECK();
     return RI_OK;
   });
@@ -428,8 +507,8 @@ int dde_grid(const Plan& p, const int4* units, int nunits, const Item* items, co
   return dispatch(p, [&]<int T, int H>() -> int {
     const dim3 g(wgs(p, nunits)), b(DT);
 #define RI_GDDE(PR, AD)                                                                                        \
-  hipLaunchKernelGGL((k_grid_dde<T, H, PR, AD>), g, b, 0, s, units, nunits, items, mask, p.coord, p.dde.w,        \
-                     p.dde.wmax, p.M, y, e, v, shrink, p.dde.patch, p.tpa)
+  hipLaunchKernelGGL((k_grid_dde<T, H, PR, AD>), g, b, 0, s, units, nunits, items, mask, p.coord, p.dde.taps,     \
+                     p.dde.wmax, p.M, p.poly, y, e, v, shrink, p.dde.patch, p.tpa)
     if (project && add_patch) RI_GDDE(true, true);
     else if (project) RI_GDDE(true, false);
     else if (add_patch) RI_GDDE(false, true);
@@ -440,20 +519,18 @@ int dde_grid(const Plan& p, const int4* units, int nunits, const Item* items, co
   });
 }
 
-int dde_merge(const Plan& p, float2* grid, bool add, hipStream_t s) {
+int dde_merge(const Plan& p, float2* grid, bool add, bool units, hipStream_t s) {
+  const int* more = units ? p.dde.more : nullptr;
   return dispatch(p, [&]<int T, int H>() -> int {
+    const dim3 g(p.windowed ? p.n_gtiles : p.n_tiles), b(DT);
     if (p.windowed && add)
-      hipLaunchKernelGGL((k_dde_merge_win<T, H, true>), dim3(p.n_gtiles), dim3(DT), 0, s, grid, p.dde.patch,
-                         p.dde.tile_has, p.K, p.tpa, p.gta);
+      hipLaunchKernelGGL((k_dde_merge_win<T, H, true>), g, b, 0, s, grid, p.dde.patch, more, p.K, p.tpa, p.gta);
     else if (p.windowed)
-      hipLaunchKernelGGL((k_dde_merge_win<T, H, false>), dim3(p.n_gtiles), dim3(DT), 0, s, grid, p.dde.patch,
-                         p.dde.tile_has, p.K, p.tpa, p.gta);
+      hipLaunchKernelGGL((k_dde_merge_win<T, H, false>), g, b, 0, s, grid, p.dde.patch, more, p.K, p.tpa, p.gta);
     else if (add)
-      hipLaunchKernelGGL((k_dde_merge<T, H, true>), dim3(p.n_tiles), dim3(DT), 0, s, grid, p.dde.patch,
-                         p.dde.tile_has, p.K, p.tpa);
+      hipLaunchKernelGGL((k_dde_merge<T, H, true>), g, b, 0, s, grid, p.dde.patch, more, p.K, p.tpa);
     else
-      hipLaunchKernelGGL((k_dde_merge<T, H, false>), dim3(p.n_tiles), dim3(DT), 0, s, grid, p.dde.patch,
-                         p.dde.tile_has, p.K, p.tpa);
+      hipLaunchKernelGGL((k_dde_merge<T, H, false>), g, b, 0, s, grid, p.dde.patch, more, p.K, p.tpa);
     RI_LAUNCH_CHECK();
     return RI_OK;
   });
@@ -495,33 +572,54 @@ extern "C" int ri_plan_dde(ri_plan plan, int jd, const float* d_host, hipStream_
     const float2* du = reinterpret_cast<const float2*>(d_host);
     for (int64_t k = 0; k < p.M; ++k)
       std::copy(du + size_t(p.order_host[k]) * jd2, du + size_t(p.order_host[k] + 1) * jd2, dp.begin() + k * jd2);
-    std::vector<uint8_t> has(p.n_tiles, 0);
-    for (const int4& u : p.tile_units_host) has[u.x] = 1;
-    const size_t S2 = size_t(dd.S) * dd.S;
+    // the tiles' units: runs of items of at most `cap` visibilities, so that the densest tiles are
+    // not one workgroup's work (300007 visibilities: 44 us at 256, 42 at 384, 41 at 512; more than
+    // 512 leaves the chip fewer units than it holds at once) and the further patches stay fewer
+    // than about 1024
+    const int64_t cap = std::max<int64_t>(ri::GRID_UNIT_VIS, p.M / 1024);
+    std::vector<int4> tunits;
+    std::vector<int> count(p.n_tiles, 0), more(size_t(p.n_tiles) + 1, p.n_tiles);
+    for (const int4& un : p.tile_units_host) {
+      int64_t acc = 0;
+      int a = un.y;
+      for (int q = un.y; q <= un.z; ++q) {
+        const int w = q < un.z ? p.titem_vis_host[q] : 0;
+        if (q < un.z && (q == a || acc + w <= cap)) {
+          acc += w;
+          continue;
+        }
+        tunits.push_back(make_int4(un.x, a, q, count[un.x]++));
+        a = q;
+        acc = w;
+      }
+    }
+    for (int t = 0; t < p.n_tiles; ++t) more[t + 1] = more[t] + std::max(0, count[t] - 1);
+    for (int4& un : tunits) un.w = un.w == 0 ? un.x : more[un.x] + un.w - 1;
     if (rc == RI_OK) rc = ri::dev_alloc(&d_dev, dp.size());
-    if (rc == RI_OK) rc = ri::dev_alloc(&dd.w, S2 * p.M);
+    if (rc == RI_OK) rc = ri::dev_alloc(&dd.taps, size_t(jd2) * p.M);
     if (rc == RI_OK) rc = ri::dev_alloc(&dd.wmax, size_t(p.M));
-    if (rc == RI_OK) rc = ri::dev_alloc(&dd.tunits, p.tile_units_host.size());
-    if (rc == RI_OK) rc = ri::dev_alloc(&dd.tile_has, size_t(p.n_tiles));
-    if (rc == RI_OK) rc = ri::dev_alloc(&dd.patch, size_t(p.n_tiles) * ri::region_cells(p));
+    if (rc == RI_OK) rc = ri::dev_alloc(&dd.tunits, tunits.size());
+    if (rc == RI_OK) rc = ri::dev_alloc(&dd.more, more.size());
+    if (rc == RI_OK) rc = ri::dev_alloc(&dd.patch, size_t(more[p.n_tiles]) * ri::region_cells(p));
     if (rc == RI_OK) {
-      dd.n_tunits = int(p.tile_units_host.size());
+      dd.n_tunits = int(tunits.size());
       if (hipMemcpyAsync(d_dev, dp.data(), dp.size() * sizeof(float2), hipMemcpyHostToDevice, stream) != hipSuccess ||
-          hipMemcpyAsync(dd.tunits, p.tile_units_host.data(), dd.n_tunits * sizeof(int4), hipMemcpyHostToDevice,
-                         stream) != hipSuccess ||
-          hipMemcpyAsync(dd.tile_has, has.data(), has.size(), hipMemcpyHostToDevice, stream) != hipSuccess)
+          hipMemcpyAsync(dd.tunits, tunits.data(), tunits.size() * sizeof(int4), hipMemcpyHostToDevice, stream) !=
+              hipSuccess ||
+          hipMemcpyAsync(dd.more, more.data(), more.size() * sizeof(int), hipMemcpyHostToDevice, stream) !=
+              hipSuccess)
         rc = fail(RI_EHIP, "copy of the DDE tables failed");
     }
     if (rc == RI_OK) rc = ri::dde_zero_patches(p, stream);
     if (rc == RI_OK) {
       const unsigned g = unsigned(std::min<int64_t>((p.M + ri::DT - 1) / ri::DT, 65536));
       switch (h) {
-        case 0: hipLaunchKernelGGL(ri::k_dde_weights<0>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.w, dd.wmax); break;
-        case 1: hipLaunchKernelGGL(ri::k_dde_weights<1>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.w, dd.wmax); break;
-        case 2: hipLaunchKernelGGL(ri::k_dde_weights<2>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.w, dd.wmax); break;
-        default: hipLaunchKernelGGL(ri::k_dde_weights<3>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.w, dd.wmax); break;
+        case 0: hipLaunchKernelGGL(ri::k_dde_taps<0>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.taps, dd.wmax); break;
+        case 1: hipLaunchKernelGGL(ri::k_dde_taps<1>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.taps, dd.wmax); break;
+        case 2: hipLaunchKernelGGL(ri::k_dde_taps<2>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.taps, dd.wmax); break;
+        default: hipLaunchKernelGGL(ri::k_dde_taps<3>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.taps, dd.wmax); break;
       }
-      if (hipGetLastError() != hipSuccess) rc = fail(RI_EHIP, "DDE weight kernel launch failed");
+      if (hipGetLastError() != hipSuccess) rc = fail(RI_EHIP, "DDE tap kernel launch failed");
     }
     if (rc == RI_OK && hipStreamSynchronize(stream) != hipSuccess) rc = fail(RI_EHIP, "stream sync failed");
   } catch (const std::bad_alloc&) {

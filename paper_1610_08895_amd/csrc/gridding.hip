@@ -912,7 +912,7 @@ int degrid_residual_block(const Plan& p, int block, const float2* grid, const fl
 int grid_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* grid, hipStream_t s) {
   if (p.dde.on()) {
     RI_TRY(dde_grid(p, p.dde.tunits, p.dde.n_tunits, p.titems, mask, y, nullptr, nullptr, nullptr, false, false, s));
-    return dde_merge(p, grid, false, s);
+    return dde_merge(p, grid, false, true, s);
   }
   if (p.windowed) return win_apply(p, y, mask, grid, s);
   return grid_units<GR_APPLY>(p, true, p.units, p.n_units, p.titems, mask, grid, y, nullptr, nullptr, nullptr,
@@ -943,7 +943,7 @@ int grid_project_all(const Plan& p, const float2* r, float2* v, const float* shr
 }
 
 int grid_halo(const Plan& p, float2* grid, hipStream_t s) {
-  if (p.dde.on()) return dde_merge(p, grid, true, s);
+  if (p.dde.on()) return dde_merge(p, grid, true, true, s);
   if (p.windowed) return RI_OK;  // no rings: the adjoint column pass adds the regions
   switch (p.tile) {
     case 16: launch_halo<16>(p, grid, true, s); break;
@@ -971,7 +971,7 @@ int grid_blocks_begin(const Plan& p, hipStream_t s) {
 }
 
 int grid_blocks_end(const Plan& p, float2* grid, hipStream_t s) {
-  if (p.dde.on()) return dde_merge(p, grid, true, s);
+  if (p.dde.on()) return dde_merge(p, grid, true, false, s);
   if (p.windowed) return RI_OK;
   switch (p.tile) {
     case 16: launch_halo<16>(p, grid, false, s); break;

@@ -403,6 +403,8 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
     for (int t : ts) units.push_back(make_int4(t, tile_cnt[t], tile_cnt[t + 1], tile_vis[t]));
   }
   p.tile_units_host = units;
+  p.titem_vis_host.clear();
+  for (int k : tile_items) p.titem_vis_host.push_back(items[k].w);
   if (p.windowed) {  // none of what follows but the degridding units
     units.clear();
     empty_tiles.clear();

@@ -77,16 +77,17 @@ constexpr int ring_cells(int tile) { return (tile + 8) * (tile + 8) - tile * til
 
 // Direction-dependent effects folded into G (Eq. 1's D, Sec. II): each visibility's row of
 // G is its DDE kernel (jd x jd taps, jd = 2h + 1) convolved with the Kaiser-Bessel kernel,
-// S = J + 2h taps per axis, stored per visibility.
+// S = J + 2h cells per axis, formed from the taps where it is used.
 struct Dde {
   int h = -1;                     // -1: no DDEs (plain G)
   int S = 0;                      // taps per axis
-  float2* w = nullptr;            // S * S * M weights, tap-major: w[t * M + m] (plan order)
+  float2* taps = nullptr;         // (2h + 1)^2 * M taps, tap-major: taps[t * M + m] (plan order)
   float* wmax = nullptr;          // M: max over taps of |Re w| + |Im w| (fixed-point bound)
-  int4* tunits = nullptr;         // whole-tile units {tile, first, end, vis} over titems
+  int4* tunits = nullptr;         // gridding units {tile, first, end, patch} over titems
   int n_tunits = 0;
-  float2* patch = nullptr;        // n_tiles * (T + S - 1)^2: each tile's gridded region
-  uint8_t* tile_has = nullptr;    // n_tiles: tile has visibilities (its patch is written)
+  float2* patch = nullptr;        // (T + S - 1)^2 cells each: the tiles' gridded regions (zero where a tile
+                                  // has no visibilities), then those of dense tiles' further units
+  int* more = nullptr;            // n_tiles + 1: tile t's further patches are [more[t], more[t + 1])
   bool on() const { return h >= 0; }
 };
 
@@ -161,6 +162,7 @@ struct Plan {
   int n_empty = 0;
   int* empty_tiles = nullptr;   // n_empty tiles without visibilities
   std::vector<int4> tile_units_host;  // whole-tile units over titems, densest first
+  std::vector<int> titem_vis_host;    // n_items: the visibilities of each of titems
   Dde dde;
   int* active_count = nullptr;
   float* norm_tmp = nullptr;  // n * n scratch for power iterations
@@ -267,12 +269,13 @@ int plan_gather_coord(const uint2* packed, const int* order, int64_t M, uint2* c
 // ---- DDE-aware G (dde.hip); used by the functions above when p.dde.on() ----
 int dde_degrid(const Plan& p, const int4* units, int nunits, const Item* items, const uint8_t* mask,
                const float2* grid, float2* out, const float2* y, const float2* v, double* part, hipStream_t s);
-// gridding over whole-tile units into the tiles' patches (ADD: added to them, per-block use)
+// gridding into the units' patches (tunits), or added to the tiles' (add_patch: one block's units)
 int dde_grid(const Plan& p, const int4* units, int nunits, const Item* items, const uint8_t* mask,
              const float2* y, const float2* e, float2* v, const float* shrink, bool project, bool add_patch,
              hipStream_t s);
-// grid (=, or += with add) the sum of the DDE tiles' patches covering each cell
-int dde_merge(const Plan& p, float2* grid, bool add, hipStream_t s);
+// grid (=, or += with add) the sum of the DDE patches covering each cell (units: those of tunits,
+// else the tiles' only)
+int dde_merge(const Plan& p, float2* grid, bool add, bool units, hipStream_t s);
 int dde_zero_patches(const Plan& p, hipStream_t s);
 void dde_destroy(Dde& dd);
 
