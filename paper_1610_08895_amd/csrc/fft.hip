@@ -163,7 +163,7 @@ __global__ __launch_bounds__(NT) void k_adj_cols_win(const float2* __restrict__ 
 template <int K, int W, int NT, bool UPD>
 __global__ __launch_bounds__(NT) void k_adj_rows(const float2* __restrict__ rows, const float* __restrict__ S,
                                                  float* __restrict__ x, const float2* __restrict__ tw,
-                                                 PrimalUpdate u) {
+                                                 PrimalUpdate u, int add) {
   constexpr int n = K / 2;
   __shared__ float2 lds[K * W];
   __shared__ float2 twl[TwLds<K, W>::size];
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(NT) void k_adj_rows(const float2* __restrict__ rows
         u.x[o] = xn;
         u.xt[o] = 2.f * xn - xo;
       } else {
-        x[o] = g;
+        x[o] = add != 0 ? x[o] + g : g;
       }
     }
   };
@@ -249,10 +249,10 @@ int adj_cols_impl(const Plan& p, const float2* grid, const SideJob* side, hipStr
 }
 
 template <int K>
-int adj_rows_impl(const Plan& p, const float2*, float* x, hipStream_t s) {
+int adj_rows_impl(const Plan& p, bool add, float* x, hipStream_t s) {
   using RC = RowCfg<K>;
   hipLaunchKernelGGL((k_adj_rows<K, RC::W, RC::NT, false>), dim3(K / 2 / RC::W), dim3(RC::NT), 0, s, p.rowbuf,
-                     p.scale, x, p.twiddle, PrimalUpdate{});
+                     p.scale, x, p.twiddle, PrimalUpdate{}, add ? 1 : 0);
   RI_LAUNCH_CHECK();
   return RI_OK;
 }
@@ -261,7 +261,7 @@ template <int K>
 int adj_rows_update_impl(const Plan& p, const PrimalUpdate& u, hipStream_t s) {
   using RC = RowCfg<K>;
   hipLaunchKernelGGL((k_adj_rows<K, RC::W, RC::NT, true>), dim3(K / 2 / RC::W), dim3(RC::NT), 0, s, p.rowbuf,
-                     p.scale, nullptr, p.twiddle, u);
+                     p.scale, nullptr, p.twiddle, u, 0);
   RI_LAUNCH_CHECK();
   return RI_OK;
 }
@@ -293,8 +293,8 @@ int fft_adjoint_cols(const Plan& p, const float2* grid, hipStream_t s, const Sid
   RI_FFT_DISPATCH(adj_cols_impl, p, grid, side, s)
 }
 
-int fft_adjoint_rows(const Plan& p, float* x, hipStream_t s) {
-  RI_FFT_DISPATCH(adj_rows_impl, p, nullptr, x, s)
+int fft_adjoint_rows(const Plan& p, float* x, hipStream_t s, bool add) {
+  RI_FFT_DISPATCH(adj_rows_impl, p, add, x, s)
 }
 
 int fft_adjoint_rows_update(const Plan& p, const PrimalUpdate& u, hipStream_t s) {

@@ -103,7 +103,8 @@ __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, i
   __shared__ __align__(16) char smem[SIDE && side_smem<GT>() > TILE_BYTES ? side_smem<GT>() : TILE_BYTES];
   if constexpr (SIDE) {
     if (int(blockIdx.x) >= ustride) {
-      side_body<GT, SIDE_DWT>(side, int(blockIdx.x) - ustride, smem);
+      // (the operator form is the reverse sweep's)
+      side_body<GT, MODE == DG_APPLY ? SIDE_DWT_GATE : SIDE_DWT>(side, int(blockIdx.x) - ustride, smem);
       return;
     }
   }
@@ -844,7 +845,7 @@ template <int T, int MODE>
 int degrid_batched_t(const Plan& p, const float2* grid, float2* out, const float2* y, const float2* v,
                      double* part, const uint8_t* mask, float2* zero, hipStream_t s, const SideJob* side) {
   const int g = wgs_for(p, p.n_dunits), extra = zero != nullptr ? p.n_empty : 0;
-  if constexpr (MODE == DG_RESIDUAL) {
+  if constexpr (MODE != DG_NORMS) {
     if (side != nullptr && side->wgs > 0) {
       hipLaunchKernelGGL((k_degrid<T, MODE, true>), dim3(g + side->wgs), dim3(GT), 0, s, p.dunits, p.n_dunits,
                          p.titems, p.item_pairs, mask, p.coord, grid, p.K, p.tpa, p.poly, out, y, v, part, g,
@@ -875,9 +876,12 @@ int degrid_batched(const Plan& p, const float2* grid, float2* out, const float2*
 
 }  // namespace
 
-int degrid_apply(const Plan& p, const float2* grid, float2* y, const uint8_t* mask, hipStream_t s) {
+int degrid_apply(const Plan& p, const float2* grid, float2* y, const uint8_t* mask, hipStream_t s,
+                 const SideJob* side) {
+  if (side != nullptr && side->wgs > 0 && (p.dde.on() || !p.windowed))
+    return fail(RI_EINVAL, "degrid_apply: no side job here");
   if (p.dde.on()) return dde_degrid(p, p.dunits, p.n_dunits, p.titems, mask, grid, y, nullptr, nullptr, nullptr, s);
-  return degrid_batched<DG_APPLY>(p, grid, y, nullptr, nullptr, nullptr, mask, s);
+  return degrid_batched<DG_APPLY>(p, grid, y, nullptr, nullptr, nullptr, mask, s, nullptr, side);
 }
 
 int degrid_residual(const Plan& p, const float2* grid, const float2* y, const float2* v, float2* e,

@@ -180,7 +180,8 @@ int fft_forward_cols(const Plan& p, float2* grid, hipStream_t s);
 // side (grids of up to SIDE_K cells per axis only): a job added to the launch, SIDE_IDWT at
 // SIDE_K and SIDE_TOP below it.
 int fft_adjoint_cols(const Plan& p, const float2* grid, hipStream_t s, const SideJob* side = nullptr);
-int fft_adjoint_rows(const Plan& p, float* x, hipStream_t s);
+// add: added to x instead of stored
+int fft_adjoint_rows(const Plan& p, float* x, hipStream_t s, bool add = false);
 // Steps 17-18 fused into the adjoint row pass: with g = Re S Z^dagger F^dagger of the
 // plan's row buffer, x <- max(0, x - tau (sigma st + varsigma g)) and xt = 2 x_new - x_old,
 // elementwise over the n x n image (g itself is not stored).
@@ -203,8 +204,10 @@ int block_stats(const Plan& p, const uint8_t* mask, double* stats, double* out, 
                 const SideJob* side = nullptr);
 // out[i] = ||y_i||^2 (FP64) for every block.
 int block_sumsq(const Plan& p, const float2* y, double* out, hipStream_t s);
-// y = G b for the items of active blocks (operator form).
-int degrid_apply(const Plan& p, const float2* grid, float2* y, const uint8_t* mask, hipStream_t s);
+// y = G b for the items of active blocks (operator form).  side (windowed plans without DDEs): a
+// SIDE_DWT_GATE job.
+int degrid_apply(const Plan& p, const float2* grid, float2* y, const uint8_t* mask, hipStream_t s,
+                 const SideJob* side = nullptr);
 // grid = G^dagger y for the active blocks (operator form; the whole grid is written, tiles
 // without visibilities set to zero).
 int grid_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* grid, hipStream_t s);
@@ -246,8 +249,9 @@ int grid_blocks_end(const Plan& p, float2* grid, hipStream_t s);
 int grid_all(const Plan& p, const float2* v, float2* grid, hipStream_t s);
 
 // ---- window.hip: the gridding of windowed plans ----
-int win_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* patch, hipStream_t s);
-// side (grids of up to SIDE_K cells per axis): a SIDE_DEEP job
+// side (grids of up to SIDE_K cells per axis): a SIDE_DEEP job, SIDE_DEEP_GATE of win_apply
+int win_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* patch, hipStream_t s,
+              const SideJob* side = nullptr);
 int win_project(const Plan& p, const float2* e, float2* v, const float* shrink, const uint8_t* mask, float2* patch,
                 hipStream_t s, const SideJob* side = nullptr);
 int win_project_all(const Plan& p, const float2* r, float2* v, const float* shrink, float2* patch, hipStream_t s,

@@ -29,7 +29,7 @@ namespace {
 __global__ __launch_bounds__(ST) void k_dwt_level(DwtArgs A, const float* __restrict__ filt,
                                                   const int* __restrict__ flen, int nx, int ny) {
   __shared__ __align__(16) char smem[DWT_SMEM];
-  dwt_body(A, filt, flen, blockIdx.x, nx, ny, smem);
+  dwt_body<false>(A, filt, flen, blockIdx.x, nx, ny, smem);
 }
 
 __global__ __launch_bounds__(ST) void k_idwt_level(IdwtArgs A, const float* __restrict__ filt,
@@ -48,14 +48,14 @@ __global__ __launch_bounds__(ST * TG) void k_idwt_top(IdwtArgs A, const float* _
 __global__ __launch_bounds__(DEEP_THREADS) void k_sara_deep(DeepArgs E, const float* __restrict__ filt,
                                                             const int* __restrict__ flen) {
   __shared__ __align__(16) char smem[DEEP_SMEM];
-  deep_body(E, filt, flen, blockIdx.x, smem);
+  deep_body<false>(E, filt, flen, blockIdx.x, smem);
 }
 
 int tiles(int outputs, int t) { return (outputs + t - 1) / t; }
 
 DwtArgs dwt_args(const Sara& S, int lev, const float* x, float* s, bool clip, float alpha, const float* wts) {
   return DwtArgs{x, S.tmp, S.tmp_stride, lev >= 2 ? S.tmp_off[lev - 1] : 0, lev < S.levels ? S.tmp_off[lev] : 0,
-                 s, S.n, S.n >> (lev - 1), lev, S.levels, S.dirac, S.nw, clip ? 1 : 0, alpha, wts};
+                 s, S.n, S.n >> (lev - 1), lev, S.levels, S.dirac, S.nw, clip ? 1 : 0, alpha, wts, nullptr, 0.f};
 }
 
 IdwtArgs idwt_args(const Sara& S, int lev, const float* s, float* x) {
@@ -212,6 +212,26 @@ bool side_jobs(const Sara& S, const float* x, float* s, float alpha, const float
   j.lower.i = idwt_args(S, 2, s, nullptr);
   j.top = SideJob{t * t, t, t, S.dfilt, S.dlen};
   j.top.i = idwt_args(S, 1, s, out);
+  return true;
+}
+
+bool side_synthesis(const Sara& S, const float* s, float* out, SideJobs& j) {
+  if (deep_first(S) != 2 || S.levels < 2) return false;
+  const int t = tiles(S.n, TS);
+  j.deep = SideJob{S.nw, 0, 0, S.dfilt, S.dlen};
+  j.deep.e = deep_args(S, const_cast<float*>(s), false, true, false, 0.f, nullptr);  // s is only read
+  j.top = SideJob{t * t, t, t, S.dfilt, S.dlen};
+  j.top.i = idwt_args(S, 1, s, out);
+  return true;
+}
+
+bool side_gated(const Sara& S, const float* x, float* s, const float* gate, float scale, float alpha, const float* wts,
+                float* out, SideJobs& j) {
+  if (deep_first(S) != 2 || !side_jobs(S, x, s, alpha, wts, out, j)) return false;
+  for (DwtArgs* a : {&j.first.a, &j.deep.e.a}) {
+    a->gate = gate;
+    a->scale = scale;
+  }
   return true;
 }
 

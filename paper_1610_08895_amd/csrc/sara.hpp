@@ -54,8 +54,10 @@ struct DwtArgs {
   int clip;
   float alpha;
   const float* wts;  // per-coefficient weights of the clip bound (layout of s), or null
+  // reverse sweep: s <- |gate| < bound ? s + scale v : 0 instead of the clip (gate: layout of s)
+  const float* gate;
+  float scale;
 };
-
 
 struct IdwtArgs {
   const float* s;
@@ -75,7 +77,7 @@ struct DeepArgs {
 
 // The sparsity branch cut into jobs that ride on the launches of the data branch, as workgroups
 // added to theirs (wgs = 0: nothing to add).
-enum { SIDE_NONE = 0, SIDE_DWT = 1, SIDE_IDWT = 2, SIDE_DEEP = 3, SIDE_TOP = 4 };
+enum { SIDE_NONE = 0, SIDE_DWT = 1, SIDE_IDWT = 2, SIDE_DEEP = 3, SIDE_TOP = 4, SIDE_DWT_GATE = 5, SIDE_DEEP_GATE = 6 };
 struct SideJob {
   int wgs = 0, nx = 0, ny = 0;
   const float* filt = nullptr;
@@ -93,6 +95,12 @@ struct SideJobs {
 // The jobs of sparsity_apply, each to run after the one before it; false if the dictionary has
 // other levels than they cover.
 bool side_jobs(const Sara& S, const float* x, float* s, float alpha, const float* wts, float* out, SideJobs& j);
+// Of the reverse sweep: out = Psi s (deep, then top), and s <- |gate| < bound ? s + scale Psi^dagger x
+// : 0, then out = Psi s (first, deep, top; of the kinds that heed the gate).  False unless the deep
+// levels start at the second.
+bool side_synthesis(const Sara& S, const float* s, float* out, SideJobs& j);
+bool side_gated(const Sara& S, const float* x, float* s, const float* gate, float scale, float alpha, const float* wts,
+                float* out, SideJobs& j);
 // The job `top` in a launch of its own.
 int side_top(const Sara& S, const SideJob& j, hipStream_t st);
 

@@ -43,8 +43,11 @@ __device__ __forceinline__ float clip_bound(const DwtArgs& A, size_t k) {
   return A.wts != nullptr ? A.alpha * A.wts[k] : A.alpha;
 }
 
-__device__ __forceinline__ void put_coef(const DwtArgs& A, size_t k, float v) {
-  A.s[k] = A.clip ? clampf(A.s[k] + v, clip_bound(A, k)) : v;
+// the new coefficient from the old one and v, its analysis (g: the gate's value)
+template <bool GATE>
+__device__ __forceinline__ float new_coef(const DwtArgs& A, float old, float bound, float g, float v) {
+  if (GATE) return fabsf(g) < bound ? fmaf(A.scale, v, old) : 0.f;
+  return A.clip ? clampf(old + v, bound) : v;
 }
 
 // One analysis level for wavelet w with filters of (compile-time) length L on an output
@@ -53,7 +56,7 @@ __device__ __forceinline__ void put_coef(const DwtArgs& A, size_t k, float v) {
 // instructions, a third of them filters and most others addresses.  With pairs, constant steps and
 // 32-bit offsets they take 9 of 17 us (36 MB written); the finest synthesis level, staged the same
 // way, 22.3 -> 18 us.
-template <int L>
+template <int L, bool GATE>
 __device__ __forceinline__ void analysis_tile(const DwtArgs& A, const float* __restrict__ hw, int w, int i0,
                                               int j0, float* in, float2* lh) {
   const float* __restrict__ gw = hw + MAX_TAPS;
@@ -80,6 +83,10 @@ __device__ __forceinline__ void analysis_tile(const DwtArgs& A, const float* __r
 #pragma unroll
       for (int c = 0; c < 4; ++c) bnd[c] = A.alpha * at_byte<const float>(A.wts + sbo, ko[c]);
   }
+  float gate[4] = {0.f, 0.f, 0.f, 0.f};
+  if (GATE && mine)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) gate[c] = at_byte<const float>(A.gate + sbo, ko[c]);
   // staged by pairs, 32 threads to a row, so that a thread's column stays and its rows step by 8;
   // the rows wrap, so those after the tile's last are loaded like the others (a load of each row
   // under its own condition would wait for the one before)
@@ -124,7 +131,7 @@ __device__ __forceinline__ void analysis_tile(const DwtArgs& A, const float* __r
     hl = fmaf(gw[t], v.x, hl);
     hh = fmaf(gw[t], v.y, hh);
   }
-  auto put = [&](int c, float v) { at_byte<float>(sb, ko[c]) = A.clip ? clampf(old[c] + v, bnd[c]) : v; };
+  auto put = [&](int c, float v) { at_byte<float>(sb, ko[c]) = new_coef<GATE>(A, old[c], bnd[c], gate[c], v); };
   if (A.level < A.levels) at_byte<float>(A.tmp + w * A.tmp_stride + A.out_off, 4u * (__umul24(qi, mo) + qj)) = ll;
   else put(0, ll);
   put(1, hi);
@@ -148,6 +155,7 @@ __device__ __forceinline__ void analysis_tile(const DwtArgs& A, const float* __r
 constexpr int DWT_RW = 2 * TO + MAX_TAPS - 2;
 constexpr int DWT_IN = (DWT_RW + STAGE_ROWS - 1) / STAGE_ROWS * STAGE_ROWS * DWT_RW * 4;  // whole steps of rows
 constexpr int DWT_SMEM = DWT_IN + DWT_RW * TO * 8;
+template <bool GATE>
 __device__ __forceinline__ void dwt_body(const DwtArgs& A, const float* __restrict__ filt,
                                          const int* __restrict__ flen, int b, int nx, int ny, char* smem) {
   float* in = reinterpret_cast<float*>(smem);
@@ -159,11 +167,13 @@ __device__ __forceinline__ void dwt_body(const DwtArgs& A, const float* __restri
   if (z == A.nw) {  // Dirac basis at level 1: coefficient = pixel
     for (int idx = threadIdx.x; idx < 4 * TO * TO; idx += ST) {
       const int r = 2 * i0 + idx / (2 * TO), c = 2 * j0 + idx % (2 * TO);
-      if (r < n && c < n) put_coef(A, size_t(r) * n + c, A.x[size_t(r) * n + c]);
+      if (r >= n || c >= n) continue;
+      const size_t k = size_t(r) * n + c;
+      A.s[k] = new_coef<GATE>(A, A.clip ? A.s[k] : 0.f, A.clip ? clip_bound(A, k) : 0.f, GATE ? A.gate[k] : 0.f, A.x[k]);
     }
     return;
   }
-#define RI_ANALYSIS(LL) analysis_tile<LL>(A, filt + z * FILT_STRIDE, z, i0, j0, in, lh)
+#define RI_ANALYSIS(LL) analysis_tile<LL, GATE>(A, filt + z * FILT_STRIDE, z, i0, j0, in, lh)
   RI_SWITCH_L(flen[z], RI_ANALYSIS)
 #undef RI_ANALYSIS
 }
@@ -384,7 +394,7 @@ __device__ __forceinline__ void top_body(const IdwtArgs& A, const float* __restr
 constexpr int DEEP_THREADS = 1024;
 constexpr int DEEP_SMEM = 3 * DEEP * DEEP * 4;
 
-template <int L>
+template <int L, bool GATE>
 __device__ __forceinline__ void deep_levels(const DeepArgs& E, const float* __restrict__ hw, int w, char* smem) {
   const float* __restrict__ gw = hw + MAX_TAPS;
   constexpr int H = L / 2;
@@ -430,9 +440,9 @@ __device__ __forceinline__ void deep_levels(const DeepArgs& E, const float* __re
         for (int b = 0; b < 4; ++b) {
           if (b == 0 && lev < A.levels) continue;
           const int r = qi + (b >> 1) * mo, q = qj + (b & 1) * mo;
-          const size_t o = size_t(r) * n + q;
-          const float v =
-              A.clip ? clampf(sc[r * DEEP + q] + c[b], clip_bound(A, size_t(w + A.dirac) * n * n + o)) : c[b];
+          const size_t o = size_t(r) * n + q, k = size_t(w + A.dirac) * n * n + o;
+          const float v = new_coef<GATE>(A, A.clip ? sc[r * DEEP + q] : 0.f, A.clip ? clip_bound(A, k) : 0.f,
+                                         GATE ? A.gate[k] : 0.f, c[b]);
           sb[o] = v;
           sc[r * DEEP + q] = v;
         }
@@ -479,9 +489,10 @@ __device__ __forceinline__ void deep_levels(const DeepArgs& E, const float* __re
   }
 }
 
+template <bool GATE>
 __device__ __forceinline__ void deep_body(const DeepArgs& E, const float* __restrict__ filt,
                                           const int* __restrict__ flen, int w, char* smem) {
-#define RI_DEEP(LL) deep_levels<LL>(E, filt + w * FILT_STRIDE, w, smem)
+#define RI_DEEP(LL) deep_levels<LL, GATE>(E, filt + w * FILT_STRIDE, w, smem)
   RI_SWITCH_L(flen[w], RI_DEEP)
 #undef RI_DEEP
 }
@@ -496,10 +507,13 @@ constexpr int side_smem() {
 
 template <int THREADS, int KIND>
 __device__ __forceinline__ void side_body(const SideJob& j, int b, char* smem) {
-  static_assert((KIND == SIDE_DWT || KIND == SIDE_IDWT) == (THREADS == ST), "the job's workgroup size");
-  if constexpr (KIND == SIDE_DWT) dwt_body(j.a, j.filt, j.flen, b, j.nx, j.ny, smem);
+  static_assert((KIND == SIDE_DWT || KIND == SIDE_DWT_GATE || KIND == SIDE_IDWT) == (THREADS == ST),
+                "the job's workgroup size");
+  if constexpr (KIND == SIDE_DWT || KIND == SIDE_DWT_GATE)
+    dwt_body<KIND == SIDE_DWT_GATE>(j.a, j.filt, j.flen, b, j.nx, j.ny, smem);
   if constexpr (KIND == SIDE_IDWT) idwt_body(j.i, j.filt, j.flen, b, j.nx, j.ny, smem);
-  if constexpr (KIND == SIDE_DEEP) deep_body(j.e, j.filt, j.flen, b, smem);
+  if constexpr (KIND == SIDE_DEEP || KIND == SIDE_DEEP_GATE)
+    deep_body<KIND == SIDE_DEEP_GATE>(j.e, j.filt, j.flen, b, smem);
   if constexpr (KIND == SIDE_TOP) top_body<TOP_GROUPS>(j.i, j.filt, j.flen, b, j.nx, j.ny, smem);
 }
 

@@ -85,10 +85,6 @@ __global__ __launch_bounds__(VT) void k_vjp_clip(size_t count, const float* __re
   }
 }
 
-__global__ __launch_bounds__(VT) void k_axpy(int n, float a, const float* __restrict__ x, float* __restrict__ y) {
-  for (int k = blockIdx.x * VT + threadIdx.x; k < n; k += gridDim.x * VT) y[k] += a * x[k];
-}
-
 // part[i * nch + ch] = sum over chunk ch of block i of r^T u, u = vbar + c phiz
 __global__ __launch_bounds__(VT) void k_ball_dot(const int64_t* __restrict__ off, const uint8_t* __restrict__ mask,
                                                  const float2* __restrict__ vbar, const float2* __restrict__ phiz,
@@ -114,37 +110,31 @@ __global__ __launch_bounds__(VT) void k_ball_dot(const int64_t* __restrict__ off
   }
 }
 
-// per block: coef[2i] (weight of u), coef[2i+1] (weight of r)
-__global__ void k_ball_coef(int d, const int64_t* __restrict__ off, const uint8_t* __restrict__ mask,
-                            const double* __restrict__ stats, const double* __restrict__ eps,
-                            const double* __restrict__ part, int nch, double* __restrict__ coef) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < d; i += gridDim.x * blockDim.x) {
-    if (mask[i] == 0) {
-      coef[2 * i] = 1.0;
-      coef[2 * i + 1] = 0.0;
-      continue;
-    }
-    const double nr = sqrt(stats[2 * i]), ep = eps[i];
-    if (!(nr > ep)) {
-      coef[2 * i] = 0.0;
-      coef[2 * i + 1] = 0.0;
-      continue;
-    }
-    const int nc = int((off[i + 1] - off[i] + BALL_CHUNK - 1) / BALL_CHUNK);
-    double ru = 0.0;
-    for (int ch = 0; ch < nc; ++ch) ru += part[size_t(i) * nch + ch];
-    coef[2 * i] = 1.0 - ep / nr;
-    coef[2 * i + 1] = ep * ru / (nr * nr * nr);
-  }
+// The weights of u and of r in block i, which every workgroup of the block sums from the partials
+// (one wavefront, in the fixed order of wave_sum): a launch for it took 2.7 us of its own.
+__device__ __forceinline__ double2 ball_coef(int i, const int64_t* __restrict__ off, bool active,
+                                             const double* __restrict__ stats, const double* __restrict__ eps,
+                                             const double* __restrict__ part, int nch) {
+  if (!active) return make_double2(1.0, 0.0);
+  const double nr = sqrt(stats[2 * i]), ep = eps[i];
+  if (!(nr > ep)) return make_double2(0.0, 0.0);
+  const int nc = int((off[i + 1] - off[i] + BALL_CHUNK - 1) / BALL_CHUNK);
+  double ru = 0.0;
+  for (int ch = threadIdx.x & 63; ch < nc; ch += 64) ru += part[size_t(i) * nch + ch];
+  ru = __shfl(wave_sum(ru), 0);
+  return make_double2(1.0 - ep / nr, ep * ru / (nr * nr * nr));
 }
 
 __global__ __launch_bounds__(VT) void k_ball_apply(const int64_t* __restrict__ off, const uint8_t* __restrict__ mask,
                                                    float2* __restrict__ vbar, const float2* __restrict__ phiz, float c,
-                                                   const float2* __restrict__ r, const double* __restrict__ coef) {
+                                                   const float2* __restrict__ r, const double* __restrict__ stats,
+                                                   const double* __restrict__ eps, const double* __restrict__ part,
+                                                   int nch) {
   const int i = blockIdx.y, ch = blockIdx.x;
   const int64_t lo = off[i] + int64_t(ch) * BALL_CHUNK, hi = min(off[i + 1], lo + BALL_CHUNK);
-  const float a = float(coef[2 * i]), b = float(coef[2 * i + 1]);
   const bool active = mask[i] != 0;
+  const double2 coef = ball_coef(i, off, active, stats, eps, part, nch);
+  const float a = float(coef.x), b = float(coef.y);
   for (int64_t m = lo + threadIdx.x; m < hi; m += VT) {
     const float2 vb = vbar[m], pz = phiz[m];
     const float2 u = make_float2(vb.x + c * pz.x, vb.y + c * pz.y);
@@ -184,12 +174,6 @@ int vjp_clip(size_t count, const float* s_new, float alpha, const float* wts, co
   return RI_OK;
 }
 
-int axpy(int n, float a, const float* x, float* y, hipStream_t s) {
-  hipLaunchKernelGGL(k_axpy, dim3(blocks_for(n)), dim3(VT), 0, s, n, a, x, y);
-  RI_LAUNCH_CHECK();
-  return RI_OK;
-}
-
 int ball_chunks(const Plan& p) {
   int64_t mx = 1;
   for (int i = 0; i < p.d; ++i) mx = std::max<int64_t>(mx, p.block_off_host[i + 1] - p.block_off_host[i]);
@@ -197,15 +181,13 @@ int ball_chunks(const Plan& p) {
 }
 
 int vjp_ball(const Plan& p, const uint8_t* mask, float2* vbar, const float2* phiz, float c, const float2* r,
-             const double* stats, const double* eps, double* part, double* coef, hipStream_t s) {
+             const double* stats, const double* eps, double* part, hipStream_t s) {
   const int nch = ball_chunks(p);
   const dim3 g(nch, p.d);
   hipLaunchKernelGGL(k_ball_dot, g, dim3(VT), 0, s, p.block_off, mask, vbar, phiz, c, r, nch, part);
   RI_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_ball_coef, dim3((p.d + 255) / 256), dim3(256), 0, s, p.d, p.block_off, mask, stats, eps, part,
-                     nch, coef);
-  RI_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_ball_apply, g, dim3(VT), 0, s, p.block_off, mask, vbar, phiz, c, r, coef);
+  hipLaunchKernelGGL(k_ball_apply, g, dim3(VT), 0, s, p.block_off, mask, vbar, phiz, c, r, stats, eps, part,
+                     nch);
   RI_LAUNCH_CHECK();
   return RI_OK;
 }

@@ -16,14 +16,12 @@ int vjp_param_grads(int n, const float* zbar, const float* st, const float* g, d
 // sbar <- (sbar + c w) [|s_new| < bound], bound = alpha, or alpha * wts[k] with weights
 int vjp_clip(size_t count, const float* s_new, float alpha, const float* wts, const float* w, float c, float* sbar,
              hipStream_t s);
-// y += a x
-int axpy(int n, float a, const float* x, float* y, hipStream_t s);
 // Per-block FP64 partials needed by vjp_ball: d * ball_chunks(p) doubles.
 int ball_chunks(const Plan& p);
-// vbar <- step-8 VJP of u = vbar + c phiz per block (see vjp.hip); part: d * ball_chunks,
-// coef: 2 d doubles of scratch.
+// vbar <- step-8 VJP of u = vbar + c phiz per block (see vjp.hip); part: d * ball_chunks doubles
+// of scratch.
 // r: v_old + G b - y of the step (RI_PD_E after it).
 int vjp_ball(const Plan& p, const uint8_t* mask, float2* vbar, const float2* phiz, float c, const float2* r,
-             const double* stats, const double* eps, double* part, double* coef, hipStream_t s);
+             const double* stats, const double* eps, double* part, hipStream_t s);
 
 }  // namespace ri

@@ -130,7 +130,8 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restri
   __shared__ __align__(16) char smem[SIDE_BYTES > int(sizeof(Shared)) ? SIDE_BYTES : int(sizeof(Shared))];
   if constexpr (SIDE) {
     if (int(blockIdx.x) >= stride) {
-      side_body<GT, SIDE_DEEP>(side, int(blockIdx.x) - stride, smem);
+      // (the operator form is the reverse sweep's)
+      side_body<GT, MODE == GR_APPLY ? SIDE_DEEP_GATE : SIDE_DEEP>(side, int(blockIdx.x) - stride, smem);
       return;
     }
   }
@@ -274,7 +275,7 @@ int launch(const Plan& p, const int* list, int nlist, const uint8_t* mask, int o
   const int g = p.persistent_wgs > 0 ? std::min(p.persistent_wgs, nlist) : nlist;
   const unsigned* coord = reinterpret_cast<const unsigned*>(p.coord);
   if (side != nullptr && side->wgs > 0) {
-    if constexpr (SPLIT == 4 && MODE != GR_APPLY) {
+    if constexpr (SPLIT == 4) {
       static_assert(256 * SPLIT == DEEP_THREADS, "the job's workgroup size");
       hipLaunchKernelGGL((k_win_grid<MODE, SPLIT, true>), dim3(g + side->wgs), dim3(256 * SPLIT), 0, s, p.gtiles,
                          list, nlist, p.woff, p.wsegs, mask, only, coord, patch, p.poly, words(y), words(e),
@@ -304,8 +305,8 @@ int grid_tiles(const Plan& p, const int* list, int nlist, const uint8_t* mask, i
 
 }  // namespace
 
-int win_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* patch, hipStream_t s) {
-  return grid_tiles<GR_APPLY>(p, nullptr, p.n_gtiles, mask, -1, patch, y, nullptr, nullptr, nullptr, false, s);
+int win_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* patch, hipStream_t s, const SideJob* side) {
+  return grid_tiles<GR_APPLY>(p, nullptr, p.n_gtiles, mask, -1, patch, y, nullptr, nullptr, nullptr, false, s, side);
 }
 
 int win_project(const Plan& p, const float2* e, float2* v, const float* shrink, const uint8_t* mask, float2* patch,
