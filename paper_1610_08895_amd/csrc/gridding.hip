@@ -84,6 +84,11 @@ static_assert((Pitch<32>::TW - 32) * Pitch<32>::TW + 32 * (Pitch<32>::TW - 32) =
 // MAX_BIN / GT) visibilities of an item before computing any, and the residual norms of
 // an item are left as one FP64 partial pair per wavefront (part[(item * NWAVES + w) * 2],
 // item = its index in block order).
+// Every load of a step is issued before any is waited for: staging a cell at a time, and loads whose
+// 64-bit addresses took the registers of loads in flight, were seven and four latencies in a row
+// (1024^2, 2^22 visibilities, beside the finest analysis level: 87 us, now 80; alone both 50, bound
+// by vector instructions, 38 us).  102 registers, 4 wavefronts per SIMD; held to 96 or 80 it
+// spills and is slower (solver 1085 us per four steps, 1122, 1243).
 // SIDE: workgroups from ustride on are those of a sparsity job instead.
 template <int T, int MODE, bool SIDE>
 __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, int nunits,
@@ -128,37 +133,52 @@ __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, i
     if (!any) continue;
     const int ty = un.x / tpa, tx = un.x - (un.x / tpa) * tpa;
     const int gy0 = ty * T - (KB_J / 2 - 1), gx0 = tx * T - (KB_J / 2 - 1);
-    for (int idx = threadIdx.x; idx < TW * TW; idx += GT) {
-      const int ly = idx / TW, lx = idx - ly * TW;
-      const int gy = (gy0 + ly) & (K - 1), gx = (gx0 + lx) & (K - 1);
-      tile[ly * TP + lx] = grid[size_t(gy) * K + gx];
+    // STEP loads in flight per thread (those past the region's last cell repeat it)
+    constexpr int PER = (TW * TW + GT - 1) / GT, STEP = PER < 7 ? PER : 7;
+#pragma unroll 1
+    for (int i0 = threadIdx.x; i0 < TW * TW; i0 += STEP * GT) {
+      float2 g[STEP];
+      int l[STEP];
+#pragma unroll
+      for (int j = 0; j < STEP; ++j) {
+        const int idx = min(i0 + j * GT, TW * TW - 1), ly = idx / TW, lx = idx - ly * TW;
+        l[j] = ly * TP + lx;
+        g[j] = grid[unsigned(((gy0 + ly) & (K - 1)) * K + ((gx0 + lx) & (K - 1)))];
+      }
+#pragma unroll
+      for (int j = 0; j < STEP; ++j) tile[l[j]] = g[j];
     }
     __syncthreads();
     for (int q = un.y; q < un.z; ++q) {
       const Item it = items[q];
       if (mask != nullptr && mask[it.x] == 0) continue;
+      // the item's arrays: a scalar address and a thread's offset, so that no load's address takes
+      // the registers of a load in flight
+      const uint2* ci = coord + it.z;
+      const float2 *yi = y + it.z, *vi = v + it.z;
+      float2* oi = out + it.z;
       uint2 c[NV];
       float2 yy[NV], vv[NV];
 #pragma unroll
       for (int k = 0; k < NV; ++k) {
-        const int s = threadIdx.x + k * GT;
-        if (s < it.w) {
-          c[k] = coord[it.z + s];
+        const unsigned s = threadIdx.x + k * GT;
+        if (int(s) < it.w) {
+          c[k] = ci[s];
           if (MODE != DG_APPLY) {
-            yy[k] = y[it.z + s];
-            vv[k] = v[it.z + s];
+            yy[k] = yi[s];
+            vv[k] = vi[s];
           }
         }
       }
       double sr = 0.0, se = 0.0;
       auto emit = [&](int k, float2 acc) {
-        const int s = threadIdx.x + k * GT;
+        const unsigned s = threadIdx.x + k * GT;
         if (MODE == DG_APPLY) {
-          out[it.z + s] = acc;
+          oi[s] = acc;
         } else {
           const float2 e = make_float2(acc.x - yy[k].x, acc.y - yy[k].y);
           const float2 r = make_float2(vv[k].x + e.x, vv[k].y + e.y);
-          if (MODE == DG_RESIDUAL) out[it.z + s] = r;
+          if (MODE == DG_RESIDUAL) oi[s] = r;
           sr += double(r.x) * r.x + double(r.y) * r.y;
           se += double(e.x) * e.x + double(e.y) * e.y;
         }
@@ -399,48 +419,55 @@ __global__ __launch_bounds__(GGT, grid_waves_per_simd<T>()) void k_grid_tiles(co
   // operands of the current item, and the raw loads of the next one
   float2 val[NV], ra[NV], rb[NV];
   uint2 crd[NV], rc[NV];
+  // (a scalar address and a thread's offset: a 64-bit address of each load would take the
+  // registers of a load in flight and wait for it; solver at 1024^2, four steps, 1076 us, now 1050)
   auto load_raw = [&](const Item& it) {
+    const uint2* ci = coord + it.z;
+    const float2 *yi = y + it.z, *ei = e + it.z, *vi = v + it.z;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      const int s = threadIdx.x + k * GGT;
-      if (s < it.w) {
-        const int m = it.z + s;
-        rc[k] = coord[m];
+      const unsigned s = threadIdx.x + k * GGT;
+      if (int(s) < it.w) {
+        rc[k] = ci[s];
         if (MODE == GR_APPLY) {
-          ra[k] = y[m];
+          ra[k] = yi[s];
         } else if (MODE == GR_FRESH) {
-          rb[k] = e[m];
+          rb[k] = ei[s];
         } else {
-          ra[k] = v[m];
-          rb[k] = e[m];
+          ra[k] = vi[s];
+          rb[k] = ei[s];
         }
       }
     }
   };
-  // values (with the dual update of step 8) and the bounds into red_b[buf], red_m[buf]
+  // values (with the dual update of step 8, stored once all operands are there) and the bounds
+  // into red_b[buf], red_m[buf]
   auto finish = [&](const Item& it, int buf) {
     const float sh = MODE != GR_APPLY ? shrink[it.x] : 0.f;
     float babs = 0.f, bmax = 0.f;
+    float2 vn[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       const int s = threadIdx.x + k * GGT;
       if (s < it.w) {
-        const int m = it.z + s;
         if (MODE == GR_APPLY) {
           val[k] = ra[k];
-        } else if (MODE == GR_FRESH) {
-          const float2 vn = make_float2(rb[k].x * sh, rb[k].y * sh);
-          v[m] = vn;
-          val[k] = vn;
         } else {
-          const float2 vn = make_float2(rb[k].x * sh, rb[k].y * sh);
-          v[m] = vn;
-          val[k] = make_float2(vn.x - ra[k].x, vn.y - ra[k].y);
+          vn[k] = make_float2(rb[k].x * sh, rb[k].y * sh);
+          val[k] = MODE == GR_FRESH ? vn[k] : make_float2(vn[k].x - ra[k].x, vn[k].y - ra[k].y);
         }
         crd[k] = rc[k];
         babs += fabsf(val[k].x) + fabsf(val[k].y);
       } else {
         val[k] = make_float2(0.f, 0.f);
+      }
+    }
+    if (MODE != GR_APPLY) {
+      float2* vi = v + it.z;
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        const unsigned s = threadIdx.x + k * GGT;
+        if (int(s) < it.w) vi[s] = vn[k];
       }
     }
     // the largest sum of one component over a slot pair (a same-cell pair adds both
