@@ -39,10 +39,10 @@ WORKLOAD = "n1024_m4m_d64"
 # the kernel each timed stage launches in the batched step
 STAGE_KERNEL = {
     "fft_rows": "k_fwd_rows<2048, 1, 256>", "fft_cols": "k_fwd_cols<2048, 8, 512>",
-    "degrid": "k_degrid<{T}, 1>", "block_norms": "k_block_stats", "grid": "k_grid_tiles<{T}, 2>",
+    "degrid": "k_degrid<{T}, 1, false>", "block_norms": "k_block_stats<false>", "grid": "k_grid_tiles<{T}, 2>",
     "grid_halo": "k_grid_halo<{T}>",
     "ifft_cols": "k_adj_cols<2048, 8, 512>", "ifft_rows": "k_adj_rows<2048, 1, 256, true> (with steps 17-18)",
-    "psi_adj": "k_dwt_level (4 launches)", "psi_synth": "k_idwt_level (3 launches) + k_idwt_top",
+    "psi_adj": "k_dwt_level (4 launches)", "psi_synth": "k_idwt_level (3 launches) + k_idwt_top<1>",
 }
 
 
@@ -87,10 +87,10 @@ def phi_bytes(n, M):
     return 100 * n * n + 16 * M
 
 
-def dde_phi_bytes(n, M, S):
+def dde_phi_bytes(n, M, jd):
     """Phi (or Phi^dagger) with DDE-aware G: the FFT part as for Phi (100N with the grid read
-    once) plus S^2 complex FP32 weights, coordinates and y per visibility."""
-    return 100 * n * n + (8 * S * S + 16) * M
+    once) plus jd^2 complex FP32 taps, coordinates and y per visibility."""
+    return 100 * n * n + (8 * jd * jd + 16) * M
 
 
 def profile_record(kernel_stage, workload, symbol=None):
@@ -361,9 +361,9 @@ def main():
         ms_d, _, _ = time_run(sol_d, Schedule(), 5, 20)
         del sol_d
         plan.set_dde(None)
-        db = dde_phi_bytes(w.n, w.M, S)
+        db = dde_phi_bytes(w.n, w.M, jd)
         extra["dde"] = {
-            "jd": jd, "taps_per_vis": S * S, "weight_bytes_per_vis": 8 * S * S, "setup_s": round(dde_setup, 2),
+            "jd": jd, "cells_per_vis": S * S, "tap_bytes_per_vis": 8 * jd * jd, "setup_s": round(dde_setup, 2),
             "phi_gvis_s": round(w.M / phid_ms / 1e6, 2), "phi_adj_gvis_s": round(w.M / phida_ms / 1e6, 2),
             "phi_ms": round(phid_ms, 4), "phi_adj_ms": round(phida_ms, 4), "phi_algorithmic_bytes": db,
             "phi_frac": round(db / (phid_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),

@@ -18,8 +18,8 @@
  *   (l_y, l_x) = (r - n/2, c - n/2).  n is a power of two, 16 <= n <= 2048.
  * Visibilities: complex float32, interleaved (re, im), M of them, stacked by data block
  *   as y = [y_1; ...; y_d] (Eq. 8).  Inside each block the library sorts visibilities
- *   into its own *plan order* (by grid tile and cell, and within a work item of one tile
- *   same-cell pairs and LDS banks); every device visibility array
+ *   into its own *plan order* (by grid tile and, within a tile, by windows of cells on grids
+ *   of up to 1024 cells per axis, else by cell, same-cell pairs and LDS banks); every device visibility array
  *   passed to or returned by the library is in plan order.  ri_plan_order() returns the
  *   map so the caller can permute its data once (see ri_plan_permute).
  * Masks: uint8 per block, nonzero = active (the set A of Algorithm 1, step 3).  A NULL
@@ -79,7 +79,9 @@ typedef struct {
   int slice_vis;      /* most visibilities one gridding workgroup accumulates for one
                          tile (default and negative: never split); a denser tile is
                          split over several workgroups whose partial tiles the halo
-                         pass merges in a fixed order                                   */
+                         pass merges in a fixed order.  Grids of up to 1024 cells per
+                         axis are gridded by tiles of 16 cells, never split: tile and bin
+                         are then those of the degridding, bin an upper limit           */
 } ri_tuning;
 
 /*
@@ -111,8 +113,8 @@ int ri_plan_permute(ri_plan plan, const float* src, float* dst, int to_plan, hip
  * of G).  The DDE of visibility m is band limited on the oversampled grid,
  * D_m(l) = sum_{p,q=-h..h} d_m[q][p] exp(-2 pi i (p l_x + q l_y) / K), so its row of G becomes
  * the jd x jd kernel d_m convolved with the Kaiser-Bessel kernel: (8 + 2h)^2 complex weights
- * per visibility, built on the device by this call and stored (S^2 * 8 bytes per
- * visibility, S = 8 + 2h).  From then on ri_phi, ri_phi_adj, ri_phi_norm and the Algorithm 1
+ * per visibility, formed where they are used from the taps, which the plan keeps (8 jd^2 bytes
+ * per visibility).  From then on ri_phi, ri_phi_adj, ri_phi_norm and the Algorithm 1
  * steps of solvers on this plan use the DDE-aware G (the adjoint with conjugate weights).
  * d_host: M * jd * jd complex float32 (host, user order of the visibilities; per
  * visibility row-major [q + h][p + h], q along v / rows, p along u / columns).
@@ -243,7 +245,9 @@ enum {
   RI_STAGE_DEGRID = 2,      /* G_i b_i, residuals, FP64 partial norms (steps 5, 8)          */
   RI_STAGE_BLOCK_NORMS = 3, /* per-block reduction of the partial norms, statistics out     */
   RI_STAGE_GRID = 4,        /* l2-ball shrink, G_i^dagger update, tile interiors (8, 9, 11) */
-  RI_STAGE_GRID_HALO = 5,   /* tile halos of the G_i^dagger update                         */
+  RI_STAGE_GRID_HALO = 5,   /* tile halos of the G_i^dagger update (not recorded on grids of
+                               up to 1024 cells per axis, whose tiles' reaches the column
+                               pass adds, unless the plan has DDEs)                        */
   RI_STAGE_IFFT_COLS = 6,   /* Z^dagger F^dagger, column pass (step 17)                     */
   RI_STAGE_IFFT_ROWS = 7,   /* Z^dagger F^dagger, row pass (step 17); in ri_pd_step it also
                                applies steps 17-18 to its output                          */
