@@ -113,8 +113,8 @@ int ri_plan_permute(ri_plan plan, const float* src, float* dst, int to_plan, hip
  * of G).  The DDE of visibility m is band limited on the oversampled grid,
  * D_m(l) = sum_{p,q=-h..h} d_m[q][p] exp(-2 pi i (p l_x + q l_y) / K), so its row of G becomes
  * the jd x jd kernel d_m convolved with the Kaiser-Bessel kernel: (8 + 2h)^2 complex weights
- * per visibility, formed where they are used from the taps, which the plan keeps (8 jd^2 bytes
- * per visibility).  From then on ri_phi, ri_phi_adj, ri_phi_norm and the Algorithm 1
+ * per visibility, formed where they are used from the taps, which the plan keeps (in two
+ * orders, 16 jd^2 bytes per visibility).  From then on ri_phi, ri_phi_adj, ri_phi_norm and the Algorithm 1
  * steps of solvers on this plan use the DDE-aware G (the adjoint with conjugate weights).
  * d_host: M * jd * jd complex float32 (host, user order of the visibilities; per
  * visibility row-major [q + h][p + h], q along v / rows, p along u / columns).

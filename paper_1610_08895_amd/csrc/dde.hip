@@ -12,8 +12,8 @@
 // S = 12), while the 25 taps they come from are 200 bytes, and the sum over p, q and the kernel's
 // taps separates into about 1500 multiply-adds, 91 cycles of a SIMD.  The taps are stored
 // tap-major, d[t * M + m], so the 64 lanes of a wavefront, which take 64 consecutive visibilities,
-// read 512 contiguous bytes per tap.  300007 visibilities, 512^2 image, jd = 5, 16 blocks: G 131 us
-// with stored weights, 30 without (13 of multiply-adds); its adjoint 148 and 41 us (15 of
+// read 512 contiguous bytes per tap, and by visibility for the adjoint, whose lanes are spread.  300007 visibilities, 512^2 image, jd = 5, 16 blocks: G 131 us
+// with stored weights, 30 without (13 of multiply-adds); its adjoint 148 and 37 us (15 of
 // multiply-adds, about as much of LDS atomics), merging the patches 19 and 16 us.
 //
 // Degridding stages a tile plus the kernel's reach in LDS, as the plain kernel does, and
@@ -215,12 +215,27 @@ __global__ __launch_bounds__(DT) void k_degrid_dde(const int4* __restrict__ unit
 // at a time, as a block's part of a tile comes, left most of a workgroup idle (blocks cut a tile
 // into pieces of a few dozen visibilities): 160 us, at 300007 visibilities and jd = 5, against 73
 // in list order and 49 with a wavefront's lanes spread over the list; 41 with room for all taps
-// of a visibility in registers at once (3 wavefronts per SIMD instead of 4).
+// of a visibility in registers at once (3 wavefronts per SIMD instead of 4), 37 with the taps read
+// by visibility (tap-major, the spread lanes fetched each line of taps up to 16 times: 2^22
+// visibilities: 810 us, now 512).
+// N taps of one visibility, two to a load (8-byte alignment).
+template <int N>
+__device__ __forceinline__ void load_taps(const float2* __restrict__ p, float2* d) {
+  typedef float tap2 __attribute__((ext_vector_type(4), aligned(8)));
+#pragma unroll
+  for (int t = 0; t + 1 < N; t += 2) {
+    const tap2 q = *reinterpret_cast<const tap2*>(p + t);
+    d[t] = make_float2(q.x, q.y);
+    d[t + 1] = make_float2(q.z, q.w);
+  }
+  d[N - 1] = p[N - 1];
+}
+
 template <int T, int H, bool PROJECT, bool ADDP>
 __global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __restrict__ units, int nunits,
                                                  const Item* __restrict__ items, const uint8_t* __restrict__ mask,
-                                                 const uint2* __restrict__ coord, const float2* __restrict__ taps,
-                                                 const float* __restrict__ wmax, int64_t M, KBPoly P,
+                                                 const uint2* __restrict__ coord, const float2* __restrict__ vtaps,
+                                                 const float* __restrict__ wmax, KBPoly P,
                                                  const float2* __restrict__ y, const float2* __restrict__ e,
                                                  float2* __restrict__ v, const float* __restrict__ shrink,
                                                  float2* __restrict__ patch, int tpa) {
@@ -305,9 +320,10 @@ __global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __r
           const float vr = val[s].x * scale, vi = val[s].y * scale;
           const uint2 c = coord[m];
           float2 d[JD * JD];  // conj(d) v
+          load_taps<JD * JD>(vtaps + m * (JD * JD), d);
 #pragma unroll
           for (int t = 0; t < JD * JD; ++t) {
-            const float2 g = taps[size_t(t) * M + m];
+            const float2 g = d[t];
             d[t] = make_float2(fmaf(g.x, vr, g.y * vi), fmaf(g.x, vi, -g.y * vr));
           }
           float wx[KB_J], wy[KB_J];
@@ -478,6 +494,7 @@ size_t region_cells(const Plan& p) {
 
 void dde_destroy(Dde& dd) {
   dev_free(dd.taps);
+  dev_free(dd.vtaps);
   dev_free(dd.wmax);
   dev_free(dd.tunits);
   dev_free(dd.more);
@@ -507,8 +524,8 @@ int dde_grid(const Plan& p, const int4* units, int nunits, const Item* items, co
   return dispatch(p, [&]<int T, int H>() -> int {
     const dim3 g(wgs(p, nunits)), b(DT);
 #define RI_GDDE(PR, AD)                                                                                        \
-  hipLaunchKernelGGL((k_grid_dde<T, H, PR, AD>), g, b, 0, s, units, nunits, items, mask, p.coord, p.dde.taps,     \
-                     p.dde.wmax, p.M, p.poly, y, e, v, shrink, p.dde.patch, p.tpa)
+  hipLaunchKernelGGL((k_grid_dde<T, H, PR, AD>), g, b, 0, s, units, nunits, items, mask, p.coord, p.dde.vtaps,    \
+                     p.dde.wmax, p.poly, y, e, v, shrink, p.dde.patch, p.tpa)
     if (project && add_patch) RI_GDDE(true, true);
     else if (project) RI_GDDE(true, false);
     else if (add_patch) RI_GDDE(false, true);
@@ -565,7 +582,6 @@ extern "C" int ri_plan_dde(ri_plan plan, int jd, const float* d_host, hipStream_
   dd.h = h;
   dd.S = ri::KB_J + 2 * h;
   int rc = RI_OK;
-  float2* d_dev = nullptr;
   try {
     // taps into plan order on the host
     std::vector<float2> dp(size_t(p.M) * jd2);
@@ -595,7 +611,7 @@ extern "C" int ri_plan_dde(ri_plan plan, int jd, const float* d_host, hipStream_
     }
     for (int t = 0; t < p.n_tiles; ++t) more[t + 1] = more[t] + std::max(0, count[t] - 1);
     for (int4& un : tunits) un.w = un.w == 0 ? un.x : more[un.x] + un.w - 1;
-    if (rc == RI_OK) rc = ri::dev_alloc(&d_dev, dp.size());
+    if (rc == RI_OK) rc = ri::dev_alloc(&dd.vtaps, dp.size());
     if (rc == RI_OK) rc = ri::dev_alloc(&dd.taps, size_t(jd2) * p.M);
     if (rc == RI_OK) rc = ri::dev_alloc(&dd.wmax, size_t(p.M));
     if (rc == RI_OK) rc = ri::dev_alloc(&dd.tunits, tunits.size());
@@ -603,7 +619,7 @@ extern "C" int ri_plan_dde(ri_plan plan, int jd, const float* d_host, hipStream_
     if (rc == RI_OK) rc = ri::dev_alloc(&dd.patch, size_t(more[p.n_tiles]) * ri::region_cells(p));
     if (rc == RI_OK) {
       dd.n_tunits = int(tunits.size());
-      if (hipMemcpyAsync(d_dev, dp.data(), dp.size() * sizeof(float2), hipMemcpyHostToDevice, stream) != hipSuccess ||
+      if (hipMemcpyAsync(dd.vtaps, dp.data(), dp.size() * sizeof(float2), hipMemcpyHostToDevice, stream) != hipSuccess ||
           hipMemcpyAsync(dd.tunits, tunits.data(), tunits.size() * sizeof(int4), hipMemcpyHostToDevice, stream) !=
               hipSuccess ||
           hipMemcpyAsync(dd.more, more.data(), more.size() * sizeof(int), hipMemcpyHostToDevice, stream) !=
@@ -614,10 +630,10 @@ extern "C" int ri_plan_dde(ri_plan plan, int jd, const float* d_host, hipStream_
     if (rc == RI_OK) {
       const unsigned g = unsigned(std::min<int64_t>((p.M + ri::DT - 1) / ri::DT, 65536));
       switch (h) {
-        case 0: hipLaunchKernelGGL(ri::k_dde_taps<0>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.taps, dd.wmax); break;
-        case 1: hipLaunchKernelGGL(ri::k_dde_taps<1>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.taps, dd.wmax); break;
-        case 2: hipLaunchKernelGGL(ri::k_dde_taps<2>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.taps, dd.wmax); break;
-        default: hipLaunchKernelGGL(ri::k_dde_taps<3>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, d_dev, p.poly, dd.taps, dd.wmax); break;
+        case 0: hipLaunchKernelGGL(ri::k_dde_taps<0>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, dd.vtaps, p.poly, dd.taps, dd.wmax); break;
+        case 1: hipLaunchKernelGGL(ri::k_dde_taps<1>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, dd.vtaps, p.poly, dd.taps, dd.wmax); break;
+        case 2: hipLaunchKernelGGL(ri::k_dde_taps<2>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, dd.vtaps, p.poly, dd.taps, dd.wmax); break;
+        default: hipLaunchKernelGGL(ri::k_dde_taps<3>, dim3(g), dim3(ri::DT), 0, stream, p.M, p.coord, dd.vtaps, p.poly, dd.taps, dd.wmax); break;
       }
       if (hipGetLastError() != hipSuccess) rc = fail(RI_EHIP, "DDE tap kernel launch failed");
     }
@@ -625,7 +641,6 @@ extern "C" int ri_plan_dde(ri_plan plan, int jd, const float* d_host, hipStream_
   } catch (const std::bad_alloc&) {
     rc = fail(RI_ENOMEM, "host allocation failed");
   }
-  ri::dev_free(d_dev);
   if (rc != RI_OK) ri::dde_destroy(dd);
   return rc;
 }

@@ -82,6 +82,7 @@ struct Dde {
   int h = -1;                     // -1: no DDEs (plain G)
   int S = 0;                      // taps per axis
   float2* taps = nullptr;         // (2h + 1)^2 * M taps, tap-major: taps[t * M + m] (plan order)
+  float2* vtaps = nullptr;        // the same by visibility: vtaps[m * (2h + 1)^2 + t]
   float* wmax = nullptr;          // M: max over taps of |Re w| + |Im w| (fixed-point bound)
   int4* tunits = nullptr;         // gridding units {tile, first, end, patch} over titems
   int n_tunits = 0;
