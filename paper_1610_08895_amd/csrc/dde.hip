@@ -206,18 +206,6 @@ __global__ __launch_bounds__(DT) void k_degrid_dde(const int4* __restrict__ unit
   }
 }
 
-// Gridding with conjugate DDE weights over units of one tile's items {tile, first, end, patch}.
-// PROJECT: the values are the step-8 dual changes (v_new = r shrink_i stored, v_new - v_old
-// gridded), else y.  The tile's region goes to the unit's patch (stored), or is added to the
-// tile's (ADDP; each tile then has one unit).  A unit is taken in groups of items of at most
-// MAX_BIN visibilities: the wavefronts take the active items in turn, list their visibilities
-// without gaps, and sum the fixed-point bound; the group's threads then take the list.  An item
-// at a time, as a block's part of a tile comes, left most of a workgroup idle (blocks cut a tile
-// into pieces of a few dozen visibilities): 160 us, at 300007 visibilities and jd = 5, against 73
-// in list order and 49 with a wavefront's lanes spread over the list; 41 with room for all taps
-// of a visibility in registers at once (3 wavefronts per SIMD instead of 4), 37 with the taps read
-// by visibility (tap-major, the spread lanes fetched each line of taps up to 16 times: 2^22
-// visibilities: 810 us, now 512).
 // N taps of one visibility, two to a load (8-byte alignment).
 template <int N>
 __device__ __forceinline__ void load_taps(const float2* __restrict__ p, float2* d) {
@@ -231,6 +219,18 @@ __device__ __forceinline__ void load_taps(const float2* __restrict__ p, float2* 
   d[N - 1] = p[N - 1];
 }
 
+// Gridding with conjugate DDE weights over units of one tile's items {tile, first, end, patch}.
+// PROJECT: the values are the step-8 dual changes (v_new = r shrink_i stored, v_new - v_old
+// gridded), else y.  The tile's region goes to the unit's patch (stored), or is added to the
+// tile's (ADDP; each tile then has one unit).  A unit is taken in groups of items of at most
+// MAX_BIN visibilities: the wavefronts take the active items in turn, list their visibilities
+// without gaps, and sum the fixed-point bound; the group's threads then take the list.  An item
+// at a time, as a block's part of a tile comes, left most of a workgroup idle (blocks cut a tile
+// into pieces of a few dozen visibilities): 160 us, at 300007 visibilities and jd = 5, against 73
+// in list order and 49 with a wavefront's lanes spread over the list; 41 with room for all taps
+// of a visibility in registers at once (3 wavefronts per SIMD instead of 4), 37 with the taps read
+// by visibility: tap-major, the spread lanes fetched each line of taps up to 16 times (at 2^22
+// visibilities, 1024^2 and jd = 5, 810 us, by visibility 512).
 template <int T, int H, bool PROJECT, bool ADDP>
 __global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __restrict__ units, int nunits,
                                                  const Item* __restrict__ items, const uint8_t* __restrict__ mask,
