@@ -19,9 +19,9 @@
 // Degridding stages a tile plus the kernel's reach in LDS, as the plain kernel does, and
 // forms y_m = sum_{q,p} d_m[q, p] (sum of the kernel's taps shifted by (q, p)).  Gridding (the
 // adjoint, conjugate weights) is owner-computes per unit of a tile's items: one workgroup
-// accumulates up to MAX_BIN visibilities at a time exactly in fixed point with 64-bit LDS integer
-// atomics (a power-of-two scale from the bound sum_m max_t(|Re W| + |Im W|) (|Re v| + |Im v|)),
-// and writes the tile's whole region (tile plus reach) to the unit's patch; a merge pass then
+// accumulates a group of about GROUP_VIS visibilities at a time exactly in fixed point with 64-bit LDS
+// integer atomics (a power-of-two scale from the largest sum of max_t |W_m| |v_m| over the
+// visibilities m in reach of one cell), and writes the tile's whole region (tile plus reach) to the unit's patch; a merge pass then
 // adds, for every grid cell, the patches of the up to four tiles whose regions cover it, in a
 // fixed order.  Results are deterministic.
 #include <algorithm>
@@ -37,6 +37,7 @@ namespace {
 constexpr int DT = 256;                 // threads per workgroup
 constexpr int DNV = MAX_BIN / DT;       // visibilities per thread per item (degridding)
 constexpr int MAX_H = 3;                // jd <= 7
+constexpr int GROUP_VIS = 512;           // visibilities that share one scale (one item may be larger)
 constexpr int GRID_UNIT_VIS = 512;      // visibilities of a gridding unit, if M is not larger than 2^19
 
 template <int T, int H>
@@ -45,6 +46,10 @@ struct DdeGeom {
   static constexpr int R0 = KB_J / 2 - 1 + H;  // reach before the tile
   static constexpr int TW = T + S - 1;         // region: tile plus reach
   static constexpr int TP = TW + 1;            // LDS pitch
+  // bins of BC x BC of the tile's cells: a region cell is in reach of visibilities of at most
+  // BW x BW adjacent bins
+  static constexpr int BC = 4, NB = T / BC;
+  static constexpr int BW = (S + BC - 2) / BC + 1 < NB ? (S + BC - 2) / BC + 1 : NB;
 };
 
 // The tap polynomials' row ty of W for taps d (any factor included): e[p] = sum_q w_y[ty - q] d[q][p],
@@ -72,8 +77,14 @@ __device__ __forceinline__ void weight_row(int ty, const float* wx, const float*
   }
 }
 
+// An upper bound of |z|, at most 8.3 % above it.
+__device__ __forceinline__ float modulus_bound(float2 z) {
+  const float a = fabsf(z.x), b = fabsf(z.y);
+  return fmaf(0.41421357f, fminf(a, b), fmaxf(a, b));
+}
+
 // One thread per visibility: its taps into tap-major order, and the bound of its weights,
-// max over the taps of |Re W| + |Im W|.
+// max over the taps of |W|.
 template <int H>
 __global__ __launch_bounds__(DT) void k_dde_taps(int64_t M, const uint2* __restrict__ coord,
                                                  const float2* __restrict__ in, KBPoly P, float2* __restrict__ taps,
@@ -96,7 +107,7 @@ __global__ __launch_bounds__(DT) void k_dde_taps(int64_t M, const uint2* __restr
       float2 row[S];
       weight_row<H>(ty, wx, wy, d, 0.f, row);
 #pragma unroll
-      for (int tx = 0; tx < S; ++tx) mx = fmaxf(mx, fabsf(row[tx].x) + fabsf(row[tx].y));
+      for (int tx = 0; tx < S; ++tx) mx = fmaxf(mx, modulus_bound(row[tx]));
     }
     wmax[m] = mx;
   }
@@ -221,16 +232,21 @@ __device__ __forceinline__ void load_taps(const float2* __restrict__ p, float2* 
 
 // Gridding with conjugate DDE weights over units of one tile's items {tile, first, end, patch}.
 // PROJECT: the values are the step-8 dual changes (v_new = r shrink_i stored, v_new - v_old
-// gridded), else y.  The tile's region goes to the unit's patch (stored), or is added to the
-// tile's (ADDP; each tile then has one unit).  A unit is taken in groups of items of at most
-// MAX_BIN visibilities: the wavefronts take the active items in turn, list their visibilities
-// without gaps, and sum the fixed-point bound; the group's threads then take the list.  An item
-// at a time, as a block's part of a tile comes, left most of a workgroup idle (blocks cut a tile
-// into pieces of a few dozen visibilities): 160 us, at 300007 visibilities and jd = 5, against 73
-// in list order and 49 with a wavefront's lanes spread over the list; 41 with room for all taps
-// of a visibility in registers at once (3 wavefronts per SIMD instead of 4), 37 with the taps read
-// by visibility: tap-major, the spread lanes fetched each line of taps up to 16 times (at 2^22
-// visibilities, 1024^2 and jd = 5, 810 us, by visibility 512).
+// gridded), else y.  The tile's region goes to the unit's patch (stored), or is added to the tile's
+// (ADDP; each tile then has one unit).  A unit is taken in groups of items of together at most
+// GROUP_VIS visibilities (or one item of up to MAX_BIN): the wavefronts take the active items in
+// turn, list their visibilities without gaps, and sum the fixed-point bound; the group's threads
+// then take the list.  An item at a time, as a block's part of a tile comes, left most of a
+// workgroup idle (blocks cut a tile into pieces of a few dozen visibilities): 160 us, at 300007
+// visibilities and jd = 5, against 73 in list order and 49 with a wavefront's lanes spread over the
+// list; 41 with room for all taps of a visibility in registers at once (3 wavefronts per SIMD
+// instead of 4), 37 with the taps read by visibility: tap-major, the spread lanes fetched each line
+// of taps up to 16 times (at 2^22 visibilities, 1024^2 and jd = 5, 810 us, by visibility 512).
+// The scale: a group's items come from many blocks, and the sum of all its bounds, which no cell
+// reaches, left few bits to each (2^21 visibilities in 64 blocks at 1024^2, error of Phi^dagger
+// 2.3e-6; 4.6e-7 with the bounds summed by bins of 4 x 4 cells and groups of 512, 5.2e-7 with 1024;
+// each item by itself, which has a scale of its own, 4.8e-7).  The bins cost 39 -> 41 us at 300007
+// visibilities, and with the smaller groups 217 -> 267 at 2^21.
 template <int T, int H, bool PROJECT, bool ADDP>
 __global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __restrict__ units, int nunits,
                                                  const Item* __restrict__ items, const uint8_t* __restrict__ mask,
@@ -240,14 +256,19 @@ __global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __r
                                                  float2* __restrict__ v, const float* __restrict__ shrink,
                                                  float2* __restrict__ patch, int tpa) {
   using G = DdeGeom<T, H>;
-  constexpr int S = G::S, TW = G::TW, TP = G::TP, JD = 2 * H + 1;
+  constexpr int S = G::S, TW = G::TW, TP = G::TP, JD = 2 * H + 1, NB = G::NB, BW = G::BW, PB = NB - BW + 1;
   constexpr int NWV = DT / 64;
+  static_assert(NB * NB <= DT, "one thread per bin, and a bin in a byte");
   __shared__ unsigned long long acci[TW * TP];
   __shared__ float2 val[MAX_BIN];
   __shared__ int vis[MAX_BIN];
+  __shared__ float amp[MAX_BIN];          // the bound of each visibility's contributions
+  __shared__ unsigned char bin[MAX_BIN];  // its bin
+  __shared__ unsigned bsum[NB * NB];      // the bins' sums of the bounds, in units of 2^-24 of their total
   __shared__ float red[NWV];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   for (int k = threadIdx.x; k < TW * TP; k += DT) acci[k] = 0ull;
+  if (threadIdx.x < NB * NB) bsum[threadIdx.x] = 0u;
   for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
     const int4 un = units[u];
     const int ty = un.x / tpa, tx = un.x - (un.x / tpa) * tpa;
@@ -271,7 +292,7 @@ __global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __r
           const int t = __shfl_up(end, o);
           if (lane >= o) end += t;
         }
-        const int fit = __popcll(__ballot(lane < have && cnt + end <= MAX_BIN));
+        const int fit = __popcll(__ballot(lane < have && (cnt + end <= GROUP_VIS || cnt + end == w)));
         full = fit < have;
         for (int i = wv; i < fit; i += NWV) {
           const int iw = __shfl(w, i), im = __shfl(it.z, i), s0 = cnt + __shfl(end, i) - iw;
@@ -288,9 +309,14 @@ __global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __r
             } else {
               x = y[m];
             }
+            const uint2 c = coord[m];
+            const float a = wmax[m] * modulus_bound(x);
             val[s0 + s] = x;
             vis[s0 + s] = int(m);
-            babs += wmax[m] * (fabsf(x.x) + fabsf(x.y));
+            amp[s0 + s] = a;
+            const int by = (int(c.y >> FRAC_BITS) - ty * T) / G::BC, bx = (int(c.x >> FRAC_BITS) - tx * T) / G::BC;
+            bin[s0 + s] = static_cast<unsigned char>(by * NB + bx);
+            babs += a;
           }
         }
         if (fit > 0) cnt += __shfl(end, fit - 1);
@@ -304,11 +330,26 @@ __global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __r
       for (int k = 0; k < NWV; ++k) bound += red[k];
       float inv = 0.f;
       if (bound > 0.f) {
-        // 2^E with bound * 2^E <= 2^30: no cell's sum of either part can leave 31 bits
+        // the largest sum of the bounds in reach of one cell (whole numbers: the same in any order)
+        const float unit = bound * (1.f / 16777216.f), per = 1.f / unit;
+        for (int s = threadIdx.x; s < cnt; s += DT) atomicAdd(&bsum[bin[s]], unsigned(amp[s] * per) + 1u);
+        __syncthreads();
+        unsigned most = 0;
+        for (int p = lane; p < PB * PB; p += 64) {
+          unsigned t = 0;
+#pragma unroll
+          for (int i = 0; i < BW; ++i)
+#pragma unroll
+            for (int j = 0; j < BW; ++j) t += bsum[(p / PB + i) * NB + p % PB + j];
+          most = max(most, t);
+        }
+        // 2^E with reach * 2^E < 2^31: no cell's sum of either part can leave 32 bits (the factor guards
+        // the bounds' own rounding and that of up to MAX_BIN contributions)
+        const float reach = wave_max(float(most)) * unit;
         int ex = 0;
-        frexpf(bound * 1.0001f, &ex);
-        const float scale = ldexpf(1.f, 30 - ex);
-        inv = ldexpf(1.f, ex - 30);
+        frexpf(reach * 1.0001f, &ex);
+        const float scale = ldexpf(1.f, 31 - ex);
+        inv = ldexpf(1.f, ex - 31);
         // neighbours in the list share cells, which one instruction's atomics would take in turn: a
         // wavefront's lanes take visibilities `nw` apart
         const int nw = (cnt + 63) / 64;
@@ -345,6 +386,7 @@ __global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __r
         }
       }
       __syncthreads();
+      if (threadIdx.x < NB * NB) bsum[threadIdx.x] = 0u;
       if (first || bound > 0.f) {
 #pragma unroll 2
         for (int c = threadIdx.x; c < TW * TW; c += DT) {

@@ -83,7 +83,7 @@ struct Dde {
   int S = 0;                      // taps per axis
   float2* taps = nullptr;         // (2h + 1)^2 * M taps, tap-major: taps[t * M + m] (plan order)
   float2* vtaps = nullptr;        // the same by visibility: vtaps[m * (2h + 1)^2 + t]
-  float* wmax = nullptr;          // M: max over taps of |Re w| + |Im w| (fixed-point bound)
+  float* wmax = nullptr;          // M: bound of |w| over the taps (fixed-point scale)
   int4* tunits = nullptr;         // gridding units {tile, first, end, patch} over titems
   int n_tunits = 0;
   float2* patch = nullptr;        // (T + S - 1)^2 cells each: the tiles' gridded regions (zero where a tile
