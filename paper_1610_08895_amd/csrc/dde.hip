@@ -16,14 +16,14 @@
 // with stored weights, 30 without (13 of multiply-adds); its adjoint 148 and 37 us (15 of
 // multiply-adds, about as much of LDS atomics), merging the patches 19 and 16 us.
 //
-// Degridding stages a tile plus the kernel's reach in LDS, as the plain kernel does, and
-// forms y_m = sum_{q,p} d_m[q, p] (sum of the kernel's taps shifted by (q, p)).  Gridding (the
+// Degridding stages a tile plus the kernel's reach in LDS, as the plain kernel does, and forms
+// y_m = sum_{q,p} d_m[q, p] (sum of the kernel's taps shifted by (q, p)).  Gridding (the
 // adjoint, conjugate weights) is owner-computes per unit of a tile's items: one workgroup
-// accumulates a group of about GROUP_VIS visibilities at a time exactly in fixed point with 64-bit LDS
-// integer atomics (a power-of-two scale from the largest sum of max_t |W_m| |v_m| over the
-// visibilities m in reach of one cell), and writes the tile's whole region (tile plus reach) to the unit's patch; a merge pass then
-// adds, for every grid cell, the patches of the up to four tiles whose regions cover it, in a
-// fixed order.  Results are deterministic.
+// accumulates a group of about GROUP_VIS visibilities at a time exactly in fixed point with
+// 64-bit LDS integer atomics (a power-of-two scale from the largest sum of max_t |W_m| |v_m|
+// over the visibilities m in reach of one cell), and writes the tile's whole region (tile plus
+// reach) to the unit's patch; a merge pass then adds, for every grid cell, the patches of the up
+// to four tiles whose regions cover it, in a fixed order.  Results are deterministic.
 #include <algorithm>
 #include <cmath>
 #include <new>
@@ -348,8 +348,9 @@ __global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __r
         const float reach = wave_max(float(most)) * unit;
         int ex = 0;
         frexpf(reach * 1.0001f, &ex);
-        const float scale = ldexpf(1.f, 31 - ex);
-        inv = ldexpf(1.f, ex - 31);
+        const int e2 = min(31 - ex, 126);  // (both powers are normal numbers)
+        const float scale = ldexpf(1.f, e2);
+        inv = ldexpf(1.f, -e2);
         // neighbours in the list share cells, which one instruction's atomics would take in turn: a
         // wavefront's lanes take visibilities `nw` apart
         const int nw = (cnt + 63) / 64;
