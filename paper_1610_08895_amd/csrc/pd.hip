@@ -509,7 +509,7 @@ int ri_pd_get(ri_pd P, int which, void* buf, size_t bytes, hipStream_t stream) {
     default: return fail(RI_EINVAL, "unknown state %d", which);
   }
   if (bytes != need) return fail(RI_EINVAL, "state %d needs %zu bytes, got %zu", which, need, bytes);
-  return ri::copy_f32(static_cast<float*>(buf), static_cast<const float*>(src), bytes / 4, stream);
+  return ri::copy_user(buf, src, bytes, buf, stream);
 }
 
 int ri_pd_set(ri_pd P, int which, const void* buf, size_t bytes, hipStream_t stream) {
@@ -541,7 +541,7 @@ int ri_pd_set(ri_pd P, int which, const void* buf, size_t bytes, hipStream_t str
     default: return fail(RI_EINVAL, "unknown state %d", which);
   }
   if (bytes != need) return fail(RI_EINVAL, "state %d needs %zu bytes, got %zu", which, need, bytes);
-  RI_TRY(ri::copy_f32(static_cast<float*>(dst), static_cast<const float*>(buf), bytes / 4, stream));
+  RI_TRY(ri::copy_user(dst, buf, bytes, buf, stream));
   if (which == RI_PD_V) return ri::refresh_sum(P, stream);
   return RI_OK;
 }

@@ -288,6 +288,8 @@ void dde_destroy(Dde& dd);
 int zero_f32(float* p, size_t n, hipStream_t s);
 // dst = src, n floats (device memory, not overlapping).
 int copy_f32(float* dst, const float* src, size_t n, hipStream_t s);
+// The same of `bytes` (a multiple of 4) where `user`, one of the two, is a caller's buffer of any kind.
+int copy_user(void* dst, const void* src, size_t bytes, const void* user, hipStream_t s);
 int zero_c64(float2* p, size_t n, hipStream_t s);
 // out[0] = sum x^2 (FP64); out holds SUMSQ_SCRATCH doubles.
 constexpr int SUMSQ_SCRATCH = 1025;

@@ -85,6 +85,25 @@ int zero_f32(float* p, size_t n, hipStream_t s) {
   return RI_OK;
 }
 
+// Device memory of the current GPU at a float's alignment, which k_copy can reach.
+static bool kernel_can_copy(const void* p) {
+  hipPointerAttribute_t a{};
+  int dev = -1;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();  // memory the runtime does not know
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == dev && reinterpret_cast<uintptr_t>(p) % sizeof(float) == 0;
+}
+
+// A caller's buffer may be any memory hipMemcpyAsync takes: host memory (a kernel would fault on pages
+// the GPU does not map), another GPU's, bytes without alignment.
+int copy_user(void* dst, const void* src, size_t bytes, const void* user, hipStream_t s) {
+  if (kernel_can_copy(user)) return copy_f32(static_cast<float*>(dst), static_cast<const float*>(src), bytes / 4, s);
+  RI_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDefault, s));
+  return RI_OK;
+}
+
 // Sixteen-byte words need both pointers and the length aligned to them; any other view of a
 // caller's buffer is copied by single floats.
 int copy_f32(float* dst, const float* src, size_t n, hipStream_t s) {
