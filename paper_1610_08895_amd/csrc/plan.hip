@@ -476,7 +476,16 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
     }
     dunits.push_back(make_int4(un.x, a, un.z, acc));
   }
-  std::stable_sort(dunits.begin(), dunits.end(), [](const int4& l, const int4& r) { return l.w > r.w; });
+  // The longest first, so that none starts when the others are done.  An item costs a windowed plan's
+  // unit as long as some 1024 visibilities do (its loads, one item after the other), so that a sparse
+  // tile with a few visibilities of each block is among the longest: by visibilities alone such tiles
+  // came last, and the launch took 37.5 us (6 visibilities per pixel at 256^2, 16 blocks over the
+  // whole plane), 59.9 (512^2), 51.4 (20 per pixel at 256^2); so 32.9, 46, 38.  The finer units of
+  // windowed plans (dunit_vis) are what leaves such tails: other plans' order is by visibilities.
+  const int item_cost = p.windowed ? 1024 : 0;
+  auto unit_cost = [&](const int4& u) { return int64_t(u.w) + int64_t(item_cost) * (u.z - u.y); };
+  std::stable_sort(dunits.begin(), dunits.end(),
+                   [&](const int4& l, const int4& r) { return unit_cost(l) > unit_cost(r); });
   p.n_dunits = int(dunits.size());
   {
     // XCD-aware order of the degridding units.  The dispatcher deals consecutive
@@ -488,6 +497,8 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
     std::vector<std::vector<int4>> per_xcd(NX);
     std::vector<int> tile_xcd(p.n_tiles, -1);
     int next = 0;
+    if (p.windowed)  // in density order also where the units' order is another
+      for (const int4& un : p.tile_units_host) tile_xcd[un.x] = next++ % NX;
     for (int k = 0; k < p.n_dunits; ++k) {
       int& x = tile_xcd[dunits[k].x];
       if (x < 0) x = next++ % NX;
