@@ -77,11 +77,12 @@ typedef struct {
                          per grid size: 8 columns at K = 2048, measured best)             */
   int persistent_wgs; /* workgroups of the gather/scatter kernels (default: one per unit) */
   int slice_vis;      /* most visibilities one gridding workgroup accumulates for one
-                         tile (default and negative: never split); a denser tile is
-                         split over several workgroups whose partial tiles the halo
-                         pass merges in a fixed order.  Grids of up to 1024 cells per
-                         axis are gridded by tiles of 16 cells, never split: tile and bin
-                         are then those of the degridding, bin an upper limit           */
+                         tile (default and negative: never split for this); a denser tile
+                         is split over several workgroups, by whole work items at the
+                         finest, whose partial tiles are merged in a fixed order.  Grids of
+                         up to 1024 cells per axis are gridded by tiles of 16 cells, whose
+                         dense ones are split in any case; tile and bin are then those of
+                         the degridding, bin an upper limit                                */
 } ri_tuning;
 
 /*

@@ -82,10 +82,14 @@ void destroy_plan(Plan& p) {
   dev_free(p.block_tmp);
   dev_free(p.halo);
   dev_free(p.empty_tiles);
-  dev_free(p.gtiles);
+  dev_free(p.wslots);
   dev_free(p.woff);
   dev_free(p.wsegs);
-  dev_free(p.btiles);
+  dev_free(p.wsplit);
+  dev_free(p.xpatch);
+  dev_free(p.bslots);
+  dev_free(p.bwoff);
+  dev_free(p.bsegs);
   dev_free(p.patch);
   dev_free(p.norm_tmp);
   dev_free(p.dsum);
@@ -187,6 +191,129 @@ double poly_hat(const KBPoly& P, double f) {
       sum += weight[k % 6] * 0.5 * 2.0 * (e + x * o) * std::cos(2.0 * M_PI * f * t);
     }
   return sum;
+}
+
+// Four wavefronts per window up to this many tiles.  Per launch with 1, 2 and 4: 12.2, 9.1, 8.5 us at
+// 64^2 (64 tiles), 24.4, 17.8, 16.1 at 256^2 (1024), 25.9, 26.8, 57.3 at 512^2 (4096): on the larger
+// grids the tiles fill the chip by themselves (one workgroup of 16 wavefronts per CU, by its LDS, is
+// 1024 windows at once), and the split only adds wavefronts without work.
+constexpr int WIN_SPLIT_TILES = 1024;
+
+// Host copies of a windowed plan's gridding lists (Plan::wslots and the following).
+struct WinLists {
+  std::vector<int> slots, woff, bslots, bwoff, block_off;
+  std::vector<int4> segs, bsegs, split;
+};
+
+// The units of the windowed gridding over all blocks, and each block's own.  A tile of 16 x 16 cells is
+// one unit, or P of them, each with the P-th part of each window's visibilities (blocks in order,
+// segments cut where a part ends): a window is the work of one to four wavefronts, which take 0.78 us
+// per 32 visibilities one after the other, so that a dense window alone decides the launch's time.
+// P is the least that leaves a window 1024 visibilities for one wavefront or 2048 for four (25 and 13
+// us; less costs ordinary coverages the merging, 5 us: a dirty image of 1.5 10^6 visibilities at 512^2
+// takes 64.7 us, with 768 65.6, with 512 69.8; with 4096 for four, 1.3 10^6 at 256^2 take 54 us instead
+// of 44) or win_split M / 4096, its share if the windows that the chip holds at once (1024 of four
+// wavefronts) had the same; and at least what slice_vis asks for, where that does not cut finer than
+// the tile's work items.  Gridding 2^20 visibilities of a Gaussian of 16 cells at 512^2: 958 -> 47 us
+// (tiles of 32 x 32 cells 4118, sliced by 4096 328), of 3 cells 6316 -> 70; 2^18 of 16 cells at 256^2
+// 122 -> 35.
+void window_lists(const std::vector<std::vector<int4>>& block_segs, const Plan& p, int64_t M, WinLists& out) {
+  const int d = int(block_segs.size());
+  auto slot = [&](const int4& sg) {  // 4 tile + window of the tile
+    const int wy = sg.w >> 16, wx = sg.w & 0xffff;
+    return 4 * ((wy / 2) * p.gta + wx / 2) + (wy % 2) * 2 + wx % 2;
+  };
+  // segments by tile and window, blocks in order
+  std::vector<int> off(4 * size_t(p.n_gtiles) + 1, 0);
+  for (const auto& v : block_segs)
+    for (const int4& sg : v) off[slot(sg) + 1] += 1;
+  for (size_t q = 0; q + 1 < off.size(); ++q) off[q + 1] += off[q];
+  std::vector<int4> segs(off.back());
+  std::vector<int> fill(off.begin(), off.end() - 1);
+  out.block_off.assign(1, 0);
+  out.bwoff.assign(1, 0);
+  std::vector<int4> mine;
+  for (int i = 0; i < d; ++i) {
+    mine = block_segs[i];
+    std::stable_sort(mine.begin(), mine.end(), [&](const int4& l, const int4& r) { return slot(l) < slot(r); });
+    for (size_t k = 0; k < mine.size();) {
+      const int t = slot(mine[k]) / 4;
+      out.bslots.push_back(t);
+      for (int w = 0; w < 4; ++w) {
+        for (; k < mine.size() && slot(mine[k]) == 4 * t + w; ++k) {
+          const int4 sg = make_int4(mine[k].x, mine[k].y, i, 0);
+          segs[fill[4 * t + w]++] = sg;
+          out.bsegs.push_back(sg);
+        }
+        out.bwoff.push_back(int(out.bsegs.size()));
+      }
+    }
+    out.block_off.push_back(int(out.bslots.size()));
+  }
+  struct Unit {
+    int slot;
+    int64_t vis;
+    int off[5];  // ranges of `parts`
+  };
+  std::vector<Unit> units;
+  std::vector<int4> parts;
+  const int64_t most = std::max<int64_t>(p.win_split == 1 ? 1024 : 2048, p.win_split * (M / 4096));
+  int extra = 0;
+  for (int t = 0; t < p.n_gtiles; ++t) {
+    int64_t vis = 0, P = 1, items = 0, in_block = 0, count[4];
+    for (int w = 0; w < 4; ++w) {
+      count[w] = 0;
+      for (int k = off[4 * t + w]; k < off[4 * t + w + 1]; ++k) count[w] += segs[k].y;
+      vis += count[w];
+      P = std::max(P, (count[w] + most - 1) / most);
+    }
+    if (p.slice_vis > 0 && vis > p.slice_vis) {
+      std::vector<std::pair<int, int64_t>> blocks;  // the tile's visibilities by block
+      for (int k = off[4 * t]; k < off[4 * t + 4]; ++k) blocks.push_back({segs[k].z, segs[k].y});
+      std::sort(blocks.begin(), blocks.end());
+      for (size_t k = 0; k < blocks.size(); ++k) {
+        in_block += blocks[k].second;
+        if (k + 1 < blocks.size() && blocks[k + 1].first == blocks[k].first) continue;
+        items += (in_block + p.bin - 1) / p.bin;
+        in_block = 0;
+      }
+      P = std::max(P, std::min(items, (vis + p.slice_vis - 1) / p.slice_vis));
+    }
+    if (P > 1) out.split.push_back(make_int4(t, extra, int(P - 1), 0));
+    int at[4];
+    int64_t used[4] = {0, 0, 0, 0};  // of segment at[w]
+    for (int w = 0; w < 4; ++w) at[w] = off[4 * t + w];
+    for (int64_t k = 0; k < P; ++k) {
+      Unit u{k == 0 ? t : p.n_gtiles + extra++, 0, {int(parts.size()), 0, 0, 0, 0}};
+      for (int w = 0; w < 4; ++w) {
+        int64_t left = count[w] * (k + 1) / P - count[w] * k / P;
+        u.vis += left;
+        while (left > 0) {
+          const int4 sg = segs[at[w]];
+          const int64_t n = std::min<int64_t>(left, sg.y - used[w]);
+          parts.push_back(make_int4(int(sg.x + used[w]), int(n), sg.z, 0));
+          left -= n;
+          used[w] += n;
+          if (used[w] == sg.y) {
+            ++at[w];
+            used[w] = 0;
+          }
+        }
+        u.off[w + 1] = int(parts.size());
+      }
+      units.push_back(u);
+    }
+  }
+  // most visibilities first: the dispatcher hands freed slots the next one
+  std::stable_sort(units.begin(), units.end(), [](const Unit& l, const Unit& r) { return l.vis > r.vis; });
+  out.woff.assign(1, 0);
+  for (const Unit& u : units) {
+    out.slots.push_back(u.slot);
+    for (int w = 0; w < 4; ++w) {
+      out.segs.insert(out.segs.end(), parts.begin() + u.off[w], parts.begin() + u.off[w + 1]);
+      out.woff.push_back(int(out.segs.size()));
+    }
+  }
 }
 
 int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t* off, int J, double beta,
@@ -331,53 +458,15 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
   p.n_items = int(items.size());
   p.n_items_info = items_info;
 
-  // windowed plans: the gridding tiles, most visibilities first (the dispatcher hands freed
-  // slots the next one, so the longest start first), and their windows' segments, blocks in order
-  std::vector<int> gtiles, woff, btiles;
-  std::vector<int4> wsegs;
+  WinLists win;
   if (p.windowed) {
     p.gta = K / GSIDE;
     p.n_gtiles = p.gta * p.gta;
-    auto slot = [&](const int4& sg) {  // 4 tile + window of the tile
-      const int wy = sg.w >> 16, wx = sg.w & 0xffff;
-      return 4 * ((wy / 2) * p.gta + wx / 2) + (wy % 2) * 2 + wx % 2;
-    };
-    std::vector<int64_t> vis(p.n_gtiles, 0), wvis(4 * size_t(p.n_gtiles), 0);
-    for (const auto& v : block_segs)
-      for (const int4& sg : v) wvis[slot(sg)] += sg.y;
-    for (size_t q = 0; q < wvis.size(); ++q) vis[q / 4] += wvis[q];
-    gtiles.resize(p.n_gtiles);
-    for (int t = 0; t < p.n_gtiles; ++t) gtiles[t] = t;
-    std::stable_sort(gtiles.begin(), gtiles.end(), [&](int a, int b) { return vis[a] > vis[b]; });
-    std::vector<int> pos(p.n_gtiles);
-    for (int u = 0; u < p.n_gtiles; ++u) pos[gtiles[u]] = u;
-    auto bucket = [&](const int4& sg) {
-      const int q = slot(sg);
-      return 4 * size_t(pos[q / 4]) + q % 4;
-    };
-    woff.assign(4 * size_t(p.n_gtiles) + 1, 0);
-    for (const auto& v : block_segs)
-      for (const int4& sg : v) woff[bucket(sg) + 1] += 1;
-    for (size_t q = 0; q + 1 < woff.size(); ++q) woff[q + 1] += woff[q];
-    wsegs.resize(woff.back());
-    std::vector<int> fill(woff.begin(), woff.end() - 1), last(p.n_gtiles, -1);
-    p.btile_off_host.assign(1, 0);
-    for (int i = 0; i < d; ++i) {
-      for (const int4& sg : block_segs[i]) {
-        const size_t q = bucket(sg);
-        wsegs[fill[q]++] = make_int4(sg.x, sg.y, i, 0);
-        if (last[q / 4] != i) {
-          last[q / 4] = i;
-          btiles.push_back(int(q / 4));
-        }
-      }
-      p.btile_off_host.push_back(int(btiles.size()));
-    }
-    // Four wavefronts per window while all of them (16 per tile) come to at most the chip's
-    // 16384 wavefront slots; on larger grids the tiles fill the chip by themselves and the
-    // split only adds empty wavefronts.  Per launch with 1, 2 and 4: 12.2, 9.1, 8.5 us at 64^2
-    // (64 tiles), 24.4, 17.8, 16.1 at 256^2 (1024), 25.9, 26.8, 57.3 at 512^2 (4096).
-    p.win_split = p.n_gtiles <= 1024 ? 4 : 1;
+    p.win_split = p.n_gtiles <= WIN_SPLIT_TILES ? 4 : 1;
+    window_lists(block_segs, p, M, win);
+    p.n_wunits = int(win.slots.size());
+    p.n_wsplit = int(win.split.size());
+    p.bwoff_host = win.block_off;
   }
 
   // items grouped by tile, and tiles grouped into the four gridding colours
@@ -560,10 +649,13 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
   RI_TRY(upload(&p.tile_sp_off, tile_sp_off, s));
   RI_TRY(upload(&p.tile_sp, tile_sp, s));
   RI_TRY(upload(&p.empty_tiles, empty_tiles, s));
-  RI_TRY(upload(&p.gtiles, gtiles, s));
-  RI_TRY(upload(&p.woff, woff, s));
-  RI_TRY(upload(&p.wsegs, wsegs, s));
-  RI_TRY(upload(&p.btiles, btiles, s));
+  RI_TRY(upload(&p.wslots, win.slots, s));
+  RI_TRY(upload(&p.woff, win.woff, s));
+  RI_TRY(upload(&p.wsegs, win.segs, s));
+  RI_TRY(upload(&p.wsplit, win.split, s));
+  RI_TRY(upload(&p.bslots, win.bslots, s));
+  RI_TRY(upload(&p.bwoff, win.bwoff, s));
+  RI_TRY(upload(&p.bsegs, win.bsegs, s));
   RI_TRY(dev_alloc(&p.grid, size_t(K) * K));
   RI_TRY(dev_alloc(&p.rowbuf, size_t(n) * K));
   if (p.n_spatch > 0) RI_TRY(dev_alloc(&p.spatch, size_t(p.n_spatch) * (p.tile + 8) * (p.tile + 8)));
@@ -573,6 +665,7 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
   RI_TRY(dev_alloc(&p.dsum, SUMSQ_SCRATCH));
   if (p.windowed) {
     RI_TRY(dev_alloc(&p.patch, p.adj_cells()));
+    RI_TRY(dev_alloc(&p.xpatch, size_t(p.n_wunits - p.n_gtiles) * PATCH_CELLS));
   } else {
     // tiles without visibilities keep an all-zero halo patch forever
     RI_TRY(dev_alloc(&p.halo, size_t(p.n_tiles) * ring_cells(p.tile)));

@@ -108,11 +108,18 @@ struct Plan {
   int n_items_info = 0;             // items of at most `bin` visibilities, as ri_plan_info counts them
   int win_split = 1;                // wavefronts per window (1 or 4)
   int gta = 0, n_gtiles = 0;        // gridding tiles per axis and in all
-  int* gtiles = nullptr;            // n_gtiles tile indices, most visibilities first
-  int* woff = nullptr;              // 4 n_gtiles + 1: ranges of wsegs, by tile (in that order) and window
-  int4* wsegs = nullptr;            // segments {first position, count, block, 0}
-  int* btiles = nullptr;            // positions in gtiles, by block
-  std::vector<int> btile_off_host;  // d + 1
+  // gridding units, most visibilities first: a tile, or one of several parts of a dense one
+  int n_wunits = 0;
+  int* wslots = nullptr;  // n_wunits: the unit's slot, its tile or n_gtiles + i, the i-th of xpatch
+  int* woff = nullptr;    // 4 n_wunits + 1: ranges of wsegs, by unit and window
+  int4* wsegs = nullptr;  // segments {first position, count, block, 0}
+  int n_wsplit = 0;
+  int4* wsplit = nullptr;    // n_wsplit {tile, first of xpatch, how many, 0}: a dense tile's further parts
+  float2* xpatch = nullptr;  // (n_wunits - n_gtiles) * PATCH_CELLS: their regions, rewritten by each launch
+  // the units of block i alone, whole tiles: [bwoff_host[i], bwoff_host[i + 1])
+  int *bslots = nullptr, *bwoff = nullptr;
+  int4* bsegs = nullptr;
+  std::vector<int> bwoff_host;  // d + 1
   float2* patch = nullptr;          // n_gtiles * PATCH_CELLS: the adjoint's work patches
   // cells of the adjoint's grid as the plan stores it
   size_t adj_cells() const { return windowed ? size_t(n_gtiles) * PATCH_CELLS : size_t(K) * K; }

@@ -117,21 +117,23 @@ __device__ __forceinline__ int wave_scan(int v) {
   return v;
 }
 
-// One workgroup per tile of 16 x 16 cells, SPLIT wavefronts per window of it, which take the
-// window's chunks in turn.  A wavefront goes through its window's segments (all blocks; those of
-// inactive blocks and, with only >= 0, of other blocks count as empty) in batches of 64, one lane
+// One workgroup per unit, a tile of 16 x 16 cells or a part of a dense one's visibilities, with SPLIT
+// wavefronts per window of it, which take the window's chunks in turn.  A wavefront goes through its
+// window's segments (all blocks; those of inactive blocks count as empty) in batches of 64, one lane
 // per segment: the prefix sums of their counts go to a table in LDS, in which each lane of a chunk
 // then finds its visibility by bisection.  The patch stays in registers until the window is done;
 // the wavefronts' patches are then summed into the tile's 23 x 23 region and stored in the tile's
-// own slot of the patch array (added to it with `add`), which nobody else writes: no atomics and
+// own slot of the patch array (added to it with `add`; a dense tile's further parts are always
+// stored, each in its own slot of xpatch, for k_win_merge), which nobody else writes: no atomics and
 // no order dependence, so results are deterministic.  The adjoint column pass adds the overlapping
 // regions.
 // SIDE: the workgroups after the tiles' are those of a sparsity job.
 template <int MODE, int SPLIT, bool SIDE>
-__global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restrict__ tiles, const int* __restrict__ list, int nlist,
+__global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restrict__ slots, int nunits,
                                                                  const int* __restrict__ woff, const int4* __restrict__ wsegs,
-                                                                 const uint8_t* __restrict__ mask, int only,
-                                                                 const unsigned* __restrict__ coord, float2* __restrict__ patch, KBPoly P,
+                                                                 const uint8_t* __restrict__ mask,
+                                                                 const unsigned* __restrict__ coord, float2* __restrict__ patch,
+                                                                 float2* __restrict__ xpatch, int ntiles, KBPoly P,
                                                                  const float* __restrict__ y, const float* __restrict__ e,
                                                                  float* __restrict__ v, const float* __restrict__ shrink, int add, int stride,
                                                                  SideJob side) {
@@ -163,8 +165,7 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restri
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, m = lane & 15, comp = g & 1, sl = lane_vis(lane);
   float* w = wbuf[wv];
-  for (int b = blockIdx.x; b < nlist; b += stride) {
-    const int u = list != nullptr ? list[b] : b;
+  for (int u = blockIdx.x; u < nunits; u += stride) {
     const int win = wv / SPLIT, first = (wv % SPLIT) * CH;
     const int s0 = woff[4 * u + win], s1 = woff[4 * u + win + 1];
     f32x4 dr = {0.f, 0.f, 0.f, 0.f}, di = {0.f, 0.f, 0.f, 0.f}, cr = dr, ci = di;
@@ -175,7 +176,6 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restri
       if (lane < nb) sg = wsegs[b0 + lane];
       bool act = lane < nb;
       if (act && mask != nullptr) act = mask[sg.z] != 0;
-      if (only >= 0) act = act && sg.z == only;
       const int cnt = act ? sg.y : 0;
       float fac = 0.f;
       if (MODE != GR_APPLY && act) fac = shrink[sg.z];
@@ -253,11 +253,13 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restri
     for (int k = 0; k < 4; ++k) d[(4 * g + k) * DP + m] = make_float2(dr[k], di[k]);
     if (lane == 0) touched[wv] = any;
     __syncthreads();
-    bool changed = !add;
+    const int slot = slots[u];
+    const bool store = !add || slot >= ntiles;
+    bool changed = store;
 #pragma unroll
     for (int k = 0; k < NW; ++k) changed = changed || touched[k] != 0;
     if (changed) {
-      float2* pt = patch + size_t(tiles[u]) * PATCH_CELLS;
+      float2* pt = slot < ntiles ? patch + size_t(slot) * PATCH_CELLS : xpatch + size_t(slot - ntiles) * PATCH_CELLS;
       for (int c = threadIdx.x; c < PATCH_CELLS; c += GT) {
         const int R = c / PATCH_W, C = c - (c / PATCH_W) * PATCH_W;
         float2 s = make_float2(0.f, 0.f);
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restri
               }
             }
           }
-        if (!add) {
+        if (store) {
           pt[c] = s;
         } else if (s.x != 0.f || s.y != 0.f) {
           const float2 old = pt[c];
@@ -287,63 +289,110 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void k_win_grid(const int* __restri
   }
 }
 
+// Adds a dense tile's further parts to its own slot: one workgroup per 64 cells of a tile, its
+// wavefronts taking every 16th part (compensated sums, so that many parts cost no bits) and then
+// summed in order.
+constexpr int MW = 16, MERGE_BLOCKS = PATCH_CELLS / 64;
+static_assert(PATCH_CELLS % 64 == 0, "whole wavefronts of cells");
+__global__ __launch_bounds__(64 * MW) void k_win_merge(const int4* __restrict__ split, float2* __restrict__ patch,
+                                                       const float2* __restrict__ xpatch) {
+  __shared__ float2 part[MW][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int4 sp = split[blockIdx.x / MERGE_BLOCKS];
+  const int c = (blockIdx.x % MERGE_BLOCKS) * 64 + lane;
+  const float2* x = xpatch + size_t(sp.y) * PATCH_CELLS + c;
+  float2 s = make_float2(0.f, 0.f), e = s;
+#pragma unroll 4
+  for (int j = wv; j < sp.z; j += MW) {
+    const float2 v = x[size_t(j) * PATCH_CELLS];
+    const float2 y = csub(v, e), t = cadd(s, y);
+    e = csub(csub(t, s), y);
+    s = t;
+  }
+  part[wv][lane] = s;
+  __syncthreads();
+  if (wv > 0) return;
+  float2* p = patch + size_t(sp.x) * PATCH_CELLS + c;
+  float2 a = *p;
+  for (int k = 0; k < MW && k < sp.z; ++k) a = cadd(a, part[k][lane]);
+  *p = a;
+}
+
 const float* words(const float2* p) { return reinterpret_cast<const float*>(p); }
 float* words(float2* p) { return reinterpret_cast<float*>(p); }
 
+struct Units {
+  const int *slots, *woff;
+  const int4* segs;
+  int n;
+};
+
 template <int MODE, int SPLIT>
-int launch(const Plan& p, const int* list, int nlist, const uint8_t* mask, int only, float2* patch, const float2* y,
-           const float2* e, float2* v, const float* shrink, bool add, hipStream_t s, const SideJob* side) {
-  const int g = p.persistent_wgs > 0 ? std::min(p.persistent_wgs, nlist) : nlist;
+int launch(const Plan& p, const Units& q, const uint8_t* mask, float2* patch, const float2* y, const float2* e,
+           float2* v, const float* shrink, bool add, hipStream_t s, const SideJob* side) {
+  const int g = p.persistent_wgs > 0 ? std::min(p.persistent_wgs, q.n) : q.n;
   const unsigned* coord = reinterpret_cast<const unsigned*>(p.coord);
   if (side != nullptr && side->wgs > 0) {
     if constexpr (SPLIT == 4) {
       static_assert(256 * SPLIT == DEEP_THREADS, "the job's workgroup size");
-      hipLaunchKernelGGL((k_win_grid<MODE, SPLIT, true>), dim3(g + side->wgs), dim3(256 * SPLIT), 0, s, p.gtiles,
-                         list, nlist, p.woff, p.wsegs, mask, only, coord, patch, p.poly, words(y), words(e),
+      hipLaunchKernelGGL((k_win_grid<MODE, SPLIT, true>), dim3(g + side->wgs), dim3(256 * SPLIT), 0, s, q.slots, q.n,
+                         q.woff, q.segs, mask, coord, patch, p.xpatch, p.n_gtiles, p.poly, words(y), words(e),
                          words(v), shrink, add ? 1 : 0, g, *side);
     } else {
       return fail(RI_EINVAL, "windowed gridding: no side job here");
     }
   } else {
-    hipLaunchKernelGGL((k_win_grid<MODE, SPLIT, false>), dim3(g), dim3(256 * SPLIT), 0, s, p.gtiles, list, nlist,
-                       p.woff, p.wsegs, mask, only, coord, patch, p.poly, words(y), words(e), words(v), shrink,
-                       add ? 1 : 0, g, SideJob{});
+    hipLaunchKernelGGL((k_win_grid<MODE, SPLIT, false>), dim3(g), dim3(256 * SPLIT), 0, s, q.slots, q.n, q.woff,
+                       q.segs, mask, coord, patch, p.xpatch, p.n_gtiles, p.poly, words(y), words(e), words(v),
+                       shrink, add ? 1 : 0, g, SideJob{});
   }
   RI_LAUNCH_CHECK();
   return RI_OK;
 }
 
-// Over the tiles listed (null: every tile, densest first; tiles without visibilities are among
-// them, so that a fresh pass also clears what the DDE kernels may have left there).
 template <int MODE>
-int grid_tiles(const Plan& p, const int* list, int nlist, const uint8_t* mask, int only, float2* patch,
-               const float2* y, const float2* e, float2* v, const float* shrink, bool add, hipStream_t s,
-               const SideJob* side = nullptr) {
-  if (nlist <= 0) return RI_OK;
-  return p.win_split == 1 ? launch<MODE, 1>(p, list, nlist, mask, only, patch, y, e, v, shrink, add, s, side)
-                          : launch<MODE, 4>(p, list, nlist, mask, only, patch, y, e, v, shrink, add, s, side);
+int grid_units(const Plan& p, const Units& q, const uint8_t* mask, float2* patch, const float2* y, const float2* e,
+               float2* v, const float* shrink, bool add, hipStream_t s, const SideJob* side = nullptr) {
+  if (q.n <= 0) return RI_OK;
+  return p.win_split == 1 ? launch<MODE, 1>(p, q, mask, patch, y, e, v, shrink, add, s, side)
+                          : launch<MODE, 4>(p, q, mask, patch, y, e, v, shrink, add, s, side);
+}
+
+// Over every unit (tiles without visibilities among them, so that a fresh pass also clears what the
+// DDE kernels may have left there), and the parts of the dense tiles together.
+template <int MODE>
+int grid_tiles(const Plan& p, const uint8_t* mask, float2* patch, const float2* y, const float2* e, float2* v,
+               const float* shrink, bool add, hipStream_t s, const SideJob* side) {
+  const Units all{p.wslots, p.woff, p.wsegs, p.n_wunits};
+  RI_TRY(grid_units<MODE>(p, all, mask, patch, y, e, v, shrink, add, s, side));
+  if (p.n_wsplit > 0) {
+    hipLaunchKernelGGL(k_win_merge, dim3(p.n_wsplit * MERGE_BLOCKS), dim3(64 * MW), 0, s, p.wsplit, patch, p.xpatch);
+    RI_LAUNCH_CHECK();
+  }
+  return RI_OK;
 }
 
 }  // namespace
 
 int win_apply(const Plan& p, const float2* y, const uint8_t* mask, float2* patch, hipStream_t s, const SideJob* side) {
-  return grid_tiles<GR_APPLY>(p, nullptr, p.n_gtiles, mask, -1, patch, y, nullptr, nullptr, nullptr, false, s, side);
+  return grid_tiles<GR_APPLY>(p, mask, patch, y, nullptr, nullptr, nullptr, false, s, side);
 }
 
 int win_project(const Plan& p, const float2* e, float2* v, const float* shrink, const uint8_t* mask, float2* patch,
                 hipStream_t s, const SideJob* side) {
-  return grid_tiles<GR_PROJECT>(p, nullptr, p.n_gtiles, mask, -1, patch, nullptr, e, v, shrink, true, s, side);
+  return grid_tiles<GR_PROJECT>(p, mask, patch, nullptr, e, v, shrink, true, s, side);
 }
 
 int win_project_all(const Plan& p, const float2* r, float2* v, const float* shrink, float2* patch, hipStream_t s,
                     const SideJob* side) {
-  return grid_tiles<GR_FRESH>(p, nullptr, p.n_gtiles, nullptr, -1, patch, nullptr, r, v, shrink, false, s, side);
+  return grid_tiles<GR_FRESH>(p, nullptr, patch, nullptr, r, v, shrink, false, s, side);
 }
 
 int win_project_block(const Plan& p, int block, const float2* e, float2* v, const float* shrink, float2* patch,
                       hipStream_t s) {
-  const int a = p.btile_off_host[block], b = p.btile_off_host[block + 1];
-  return grid_tiles<GR_PROJECT>(p, p.btiles + a, b - a, nullptr, block, patch, nullptr, e, v, shrink, true, s);
+  const int a = p.bwoff_host[block], b = p.bwoff_host[block + 1];
+  const Units mine{p.bslots + a, p.bwoff + 4 * a, p.bsegs, b - a};
+  return grid_units<GR_PROJECT>(p, mine, nullptr, patch, nullptr, e, v, shrink, true, s);
 }
 
 }  // namespace ri
