@@ -89,6 +89,11 @@ static_assert((Pitch<32>::TW - 32) * Pitch<32>::TW + 32 * (Pitch<32>::TW - 32) =
 // (1024^2, 2^22 visibilities, beside the finest analysis level: 87 us, now 80; alone both 50, bound
 // by vector instructions, 38 us).  102 registers, 4 wavefronts per SIMD; held to 96 or 80 it
 // spills and is slower (solver 1085 us per four steps, 1122, 1243).
+// Short items (a block's few visibilities of a tile) occupy one wavefront each, and the four take
+// turns at being that one: nothing orders them between a unit's items, so that four chains of
+// loads run side by side.  With the fewer wavefronts that these registers leave, one chain cost
+// more than before (512 blocks over the whole plane, 2^21 visibilities at 1024^2: Phi 1442 ->
+// 1823 us; with turns 963).
 // SIDE: workgroups from ustride on are those of a sparsity job instead.
 template <int T, int MODE, bool SIDE>
 __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, int nunits,
@@ -116,7 +121,7 @@ __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, i
   // the data branch's kernels issue ahead of the sparsity branch's waves sharing their SIMDs
   __builtin_amdgcn_s_setprio(3);
   float2* tile = reinterpret_cast<float2*>(smem);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (int(blockIdx.x) >= ustride) {
     // a further workgroup: zeroes the interior of one tile without visibilities in
     // zero_grid (a grid that the step's gridding will rebuild, untouched until then)
@@ -152,6 +157,7 @@ __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, i
     for (int q = un.y; q < un.z; ++q) {
       const Item it = items[q];
       if (mask != nullptr && mask[it.x] == 0) continue;
+      const int rw = (wv + q) & (NWV - 1), t = rw * 64 + lane;
       // the item's arrays: a scalar address and a thread's offset, so that no load's address takes
       // the registers of a load in flight
       const uint2* ci = coord + it.z;
@@ -161,7 +167,7 @@ __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, i
       float2 yy[NV], vv[NV];
 #pragma unroll
       for (int k = 0; k < NV; ++k) {
-        const unsigned s = threadIdx.x + k * GT;
+        const unsigned s = t + k * GT;
         if (int(s) < it.w) {
           c[k] = ci[s];
           if (MODE != DG_APPLY) {
@@ -172,7 +178,7 @@ __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, i
       }
       double sr = 0.0, se = 0.0;
       auto emit = [&](int k, float2 acc) {
-        const unsigned s = threadIdx.x + k * GT;
+        const unsigned s = t + k * GT;
         if (MODE == DG_APPLY) {
           oi[s] = acc;
         } else {
@@ -238,8 +244,8 @@ __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, i
       const uint32_t npair = item_pairs[it.y];
 #pragma unroll
       for (int j = 0; j < NV / 2; ++j) {
-        const int k = 2 * j, s = threadIdx.x + k * GT;
-        if (threadIdx.x < int((npair >> (16 * j)) & 0xffffu)) {
+        const int k = 2 * j, s = t + k * GT;
+        if (t < int((npair >> (16 * j)) & 0xffffu)) {
           pair(k, k + 1);
         } else {
           if (s < it.w) single(k);
@@ -250,8 +256,8 @@ __global__ __launch_bounds__(GT) void k_degrid(const int4* __restrict__ units, i
         sr = wave_sum(sr);
         se = wave_sum(se);
         if (lane == 0) {
-          part[(size_t(it.y) * NWV + wv) * 2] = sr;
-          part[(size_t(it.y) * NWV + wv) * 2 + 1] = se;
+          part[(size_t(it.y) * NWV + rw) * 2] = sr;
+          part[(size_t(it.y) * NWV + rw) * 2 + 1] = se;
         }
       }
     }

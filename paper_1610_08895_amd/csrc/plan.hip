@@ -566,10 +566,10 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
     dunits.push_back(make_int4(un.x, a, un.z, acc));
   }
   // The longest first, so that none starts when the others are done.  An item costs a windowed plan's
-  // unit as long as some 1024 visibilities do (its loads, one item after the other), so that a sparse
-  // tile with a few visibilities of each block is among the longest: by visibilities alone such tiles
-  // came last, and the launch took 37.5 us (6 visibilities per pixel at 256^2, 16 blocks over the
-  // whole plane), 59.9 (512^2), 51.4 (20 per pixel at 256^2); so 32.9, 46, 38.  The finer units of
+  // unit as long as some hundreds of visibilities do (its loads), so that a sparse tile with a few
+  // visibilities of each block is among the longest: by visibilities alone such tiles came last, and the
+  // launch took 27.7 us (6 visibilities per pixel at 256^2, 16 blocks over the whole plane), 37.4 (20 per
+  // pixel), 40.7 (3.8 at 512^2); so 22.1, 30.9, 35.3, with 256 per item as with 1024.  The finer units of
   // windowed plans (dunit_vis) are what leaves such tails: other plans' order is by visibilities.
   const int item_cost = p.windowed ? 1024 : 0;
   auto unit_cost = [&](const int4& u) { return int64_t(u.w) + int64_t(item_cost) * (u.z - u.y); };
