@@ -219,31 +219,24 @@ struct WinLists {
 // 122 -> 35.
 void window_lists(const std::vector<std::vector<int4>>& block_segs, const Plan& p, int64_t M, WinLists& out) {
   const int d = int(block_segs.size());
-  auto slot = [&](const int4& sg) {  // 4 tile + window of the tile
-    const int wy = sg.w >> 16, wx = sg.w & 0xffff;
-    return 4 * ((wy / 2) * p.gta + wx / 2) + (wy % 2) * 2 + wx % 2;
-  };
   // segments by tile and window, blocks in order
   std::vector<int> off(4 * size_t(p.n_gtiles) + 1, 0);
   for (const auto& v : block_segs)
-    for (const int4& sg : v) off[slot(sg) + 1] += 1;
+    for (const int4& sg : v) off[sg.w + 1] += 1;
   for (size_t q = 0; q + 1 < off.size(); ++q) off[q + 1] += off[q];
   std::vector<int4> segs(off.back());
   std::vector<int> fill(off.begin(), off.end() - 1);
   out.block_off.assign(1, 0);
   out.bwoff.assign(1, 0);
-  std::vector<int4> mine;
-  for (int i = 0; i < d; ++i) {
-    mine = block_segs[i];
-    std::stable_sort(mine.begin(), mine.end(), [&](const int4& l, const int4& r) { return slot(l) < slot(r); });
-    for (size_t k = 0; k < mine.size();) {
-      const int t = slot(mine[k]) / 4;
+  out.bsegs.reserve(segs.size());
+  for (const auto& v : block_segs) {
+    for (size_t k = 0; k < v.size();) {
+      const int t = v[k].w / 4;
       out.bslots.push_back(t);
       for (int w = 0; w < 4; ++w) {
-        for (; k < mine.size() && slot(mine[k]) == 4 * t + w; ++k) {
-          const int4 sg = make_int4(mine[k].x, mine[k].y, i, 0);
-          segs[fill[4 * t + w]++] = sg;
-          out.bsegs.push_back(sg);
+        for (; k < v.size() && v[k].w == 4 * t + w; ++k) {
+          segs[fill[v[k].w]++] = v[k];
+          out.bsegs.push_back(v[k]);
         }
         out.bwoff.push_back(int(out.bsegs.size()));
       }
@@ -257,6 +250,7 @@ void window_lists(const std::vector<std::vector<int4>>& block_segs, const Plan& 
   };
   std::vector<Unit> units;
   std::vector<int4> parts;
+  parts.reserve(segs.size());
   const int64_t most = std::max<int64_t>(p.win_split == 1 ? 1024 : 2048, p.win_split * (M / 4096));
   int extra = 0;
   for (int t = 0; t < p.n_gtiles; ++t) {
@@ -307,6 +301,7 @@ void window_lists(const std::vector<std::vector<int4>>& block_segs, const Plan& 
   // most visibilities first: the dispatcher hands freed slots the next one
   std::stable_sort(units.begin(), units.end(), [](const Unit& l, const Unit& r) { return l.vis > r.vis; });
   out.woff.assign(1, 0);
+  out.segs.reserve(parts.size());
   for (const Unit& u : units) {
     out.slots.push_back(u.slot);
     for (int w = 0; w < 4; ++w) {
@@ -373,7 +368,8 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
   p.order_host.resize(M);
   std::vector<std::vector<Item>> block_items(d);
   std::vector<std::vector<uint32_t>> block_pairs(d), block_boxes(d);
-  std::vector<std::vector<int4>> block_segs(d);  // {first position, count, block, window row << 16 | column}
+  // {first position, count, block, 4 gridding tile + its window}, by the last
+  std::vector<std::vector<int4>> block_segs(d);
   // Windowed plans keep the sorted order.  Their degridding items are cut smaller where M would
   // not give every CU four workgroups (8192 visibilities at 64^2: 14.8 us with items of up to
   // 1024 and units of 2048, 6.0 with 256 and 256), unless the (block, tile) runs alone may come
@@ -428,11 +424,13 @@ int create_plan(Plan& p, int n, int64_t M, const float* uv, int d, const int64_t
         int64_t z = a + 1;
         while (z < e && int(uint32_t(kv[z].first) >> 6) == sub) ++z;
         const int wy = int(tile) / tpa * wpt + sub / wpt, wx = int(tile) % tpa * wpt + sub % wpt;
-        block_segs[i].push_back(make_int4(int(lo + a), int(z - a), i, (wy << 16) | wx));
+        block_segs[i].push_back(make_int4(int(lo + a), int(z - a), i,
+                                          4 * ((wy / 2) * (K / GSIDE) + wx / 2) + (wy % 2) * 2 + wx % 2));
         a = z;
       }
       k = e;
     }
+    std::sort(block_segs[i].begin(), block_segs[i].end(), [](const int4& l, const int4& r) { return l.w < r.w; });
     for (int64_t k = 0; k < hi - lo; ++k) p.order_host[lo + k] = int(kv[k].second);
   };
   {
