@@ -239,16 +239,19 @@ __device__ __forceinline__ void load_taps(const float2* __restrict__ p, float2* 
 // then take the list.  An item at a time, as a block's part of a tile comes, left most of a
 // workgroup idle (blocks cut a tile into pieces of a few dozen visibilities): 160 us, at 300007
 // visibilities and jd = 5, against 73 in list order and 49 with a wavefront's lanes spread over the
-// list; 41 with room for all taps of a visibility in registers at once (3 wavefronts per SIMD
-// instead of 4), 37 with the taps read by visibility: tap-major, the spread lanes fetched each line
-// of taps up to 16 times (at 2^22 visibilities, 1024^2 and jd = 5, 810 us, by visibility 512).
+// list; 41 with room for all taps of a visibility in registers at once, 37 with the taps read by
+// visibility: tap-major, the spread lanes fetched each line of taps up to 16 times (at 2^22
+// visibilities, 1024^2 and jd = 5, 810 us, by visibility 512). 128 registers hold the taps up to jd
+// = 5, and four wavefronts per SIMD: with three, the per-block form, whose workgroups are short and
+// many, waits for slots (64 blocks over the whole plane, 200000 visibilities at 512^2: 560 us, now
+// 398), and 2^21 visibilities take 268 us instead of 246.
 // The scale: a group's items come from many blocks, and the sum of all its bounds, which no cell
 // reaches, left few bits to each (2^21 visibilities in 64 blocks at 1024^2, error of Phi^dagger
 // 2.3e-6; 4.6e-7 with the bounds summed by bins of 4 x 4 cells and groups of 512, 5.2e-7 with 1024;
 // each item by itself, which has a scale of its own, 4.8e-7).  The bins cost 39 -> 41 us at 300007
-// visibilities, and with the smaller groups 217 -> 267 at 2^21.
+// visibilities, and with the smaller groups 217 -> 246 at 2^21.
 template <int T, int H, bool PROJECT, bool ADDP>
-__global__ __launch_bounds__(DT, H <= 2 ? 3 : 2) void k_grid_dde(const int4* __restrict__ units, int nunits,
+__global__ __launch_bounds__(DT, H <= 2 ? 4 : 2) void k_grid_dde(const int4* __restrict__ units, int nunits,
                                                  const Item* __restrict__ items, const uint8_t* __restrict__ mask,
                                                  const uint2* __restrict__ coord, const float2* __restrict__ vtaps,
                                                  const float* __restrict__ wmax, KBPoly P,
