@@ -86,9 +86,10 @@ static_assert((Pitch<32>::TW - 32) * Pitch<32>::TW + 32 * (Pitch<32>::TW - 32) =
 // item = its index in block order).
 // Every load of a step is issued before any is waited for: staging a cell at a time, and loads whose
 // 64-bit addresses took the registers of loads in flight, were seven and four latencies in a row
-// (1024^2, 2^22 visibilities, beside the finest analysis level: 87 us, now 80; alone both 50, bound
-// by vector instructions, 38 us).  102 registers, 4 wavefronts per SIMD; held to 96 or 80 it
-// spills and is slower (solver 1085 us per four steps, 1122, 1243).
+// (1024^2, 2^22 visibilities: the residual form beside the finest analysis level 87 us, now 80, and
+// alone 64, now 59; the operator form alone 49, 38 of them vector instructions).  100 registers, 4
+// wavefronts per SIMD; held to 96 or 80 it spills and is slower (solver 1085 us per four steps,
+// 1122, 1243).
 // Short items (a block's few visibilities of a tile) occupy one wavefront each, and the four take
 // turns at being that one: nothing orders them between a unit's items, so that four chains of
 // loads run side by side.  With the fewer wavefronts that these registers leave, one chain cost

@@ -198,7 +198,9 @@ struct PrimalUpdate {
   float* x;
   float* xt;
   float tau, sigma, varsigma;
-  float varsigma_lo;  // what varsigma lost in rounding (added on grids of up to WINDOWED_K)
+  // what varsigma lost in rounding; added on grids of up to WINDOWED_K, where it showed in gradients of
+  // unrolled runs (larger grids keep the results they had)
+  float varsigma_lo;
 };
 int fft_adjoint_rows_update(const Plan& p, const PrimalUpdate& u, hipStream_t s);
 

@@ -20,17 +20,19 @@
 // loses bits with their number.  65536 visibilities in one window of a 512^2 image, error of
 // Phi^dagger against FP64, one chain -> chunks: equal samples 2.7e-4 -> 4.8e-7, ones at random places
 // 3.1e-5 -> 1.6e-7, random values 2.5e-6 -> 4.3e-7 (gridding.hip's integer sums: 2.1e-6, 3.0e-7,
-// 1.7e-6).  It costs 32 of a chunk's vector instructions: 1.5 10^6 visibilities at 512^2, 42 -> 44.6 us.
+// 1.7e-6).  It costs 32 vector instructions a chunk: the adjoint of 1.5 10^6 visibilities at 512^2, the
+// whole call 63.1 -> 64.5 us.
 //
 // Why only small grids: the matrix product takes 16 cycles of a SIMD's matrix unit per
 // visibility, the placing and the loads as much again on the VALU and the LDS, and together
 // they are no faster than gridding.hip's 64 atomics per visibility on a chip that those keep
-// full (2^22 visibilities at 1024^2: 98 us here, 92 us there).  But a 32 x 32 tile per
+// full (2^22 visibilities at 1024^2: 98 us here, before the sums were compensated, 92 us there).  But a 32 x 32 tile per
 // workgroup leaves most of the chip idle on a small grid and its densest tile decides the time;
-// a window per wavefront or less spreads the same work over 16 times as many.  Per launch, tiles
-// with their halo pass -> windows: 2^13 visibilities at 64^2 25.3 -> 8.5 us, 82000 of 327680
-// (masked) at 256^2 46 -> 16.1, 500000 of 10^6 (masked) at 512^2 66 -> 25.9, 1.5 10^6 at 512^2
-// 92.9 -> 35.6; the error of Phi^dagger at the last 1.9e-6 -> 4.5e-7.
+// a window per wavefront or less spreads the same work over 16 times as many.  Per launch in the
+// solver and the adjoint, tiles with their halo pass -> windows: 2^13 visibilities at 64^2 25.3 ->
+// 10.8 us and 82000 of 327680 (masked) at 256^2 47 -> 24 (both with the deep wavelet levels in the
+// launch), 500000 of 10^6 (masked) at 512^2 67 -> 26.6, 1.5 10^6 (a tenth of them spread evenly) at
+// 512^2 92.6 -> 37; the error of Phi^dagger at the last 1.9e-6 -> 4.0e-7.
 #include <algorithm>
 
 #include "plan.hpp"
